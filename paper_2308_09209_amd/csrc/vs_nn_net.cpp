@@ -27,7 +27,6 @@ struct vs_nn {
     uint16_t* hid[VS_NN_MAX_LAYERS] = {};    // hidden activations of layers 0 .. L-2, [pixels][cout]
     float* pred = nullptr;                   // [pixels][cout of the last layer]
     uint16_t* dz[2] = {};                    // [pixels][32] gradients (ping-pong)
-    uint16_t* dh = nullptr;                  // [pixels][32]
     float* scratch = nullptr;
     size_t scratch_bytes = 0;
     float* block_loss = nullptr;             // [pixels / 256 + 1]
@@ -162,7 +161,7 @@ vs_status vs_nn_create(const vs_nn_spec* spec, uint64_t seed, vs_nn** out)
         bytes += 2 * al(nw * 2);
         if (l + 1 < L) bytes += al((size_t)P * spec->cout[l] * 2);
     }
-    bytes += al((size_t)P * spec->cout[L - 1] * 4) + 3 * al((size_t)P * 32 * 2) + al(n->scratch_bytes) +
+    bytes += al((size_t)P * spec->cout[L - 1] * 4) + 2 * al((size_t)P * 32 * 2) + al(n->scratch_bytes) +
              al(((size_t)P / 256 + 1) * 4);
     if (hipMalloc(&n->mem, bytes) != hipSuccess) {
         vs_nn_destroy(n);
@@ -187,7 +186,6 @@ vs_status vs_nn_create(const vs_nn_spec* spec, uint64_t seed, vs_nn** out)
     n->pred = (float*)take((size_t)P * spec->cout[L - 1] * 4);
     n->dz[0] = (uint16_t*)take((size_t)P * 32 * 2);
     n->dz[1] = (uint16_t*)take((size_t)P * 32 * 2);
-    n->dh = (uint16_t*)take((size_t)P * 32 * 2);
     n->scratch = (float*)take(n->scratch_bytes);
     n->block_loss = (float*)take(((size_t)P / 256 + 1) * 4);
     // He initialisation over the live inputs (the first layer reads in_live
@@ -236,10 +234,13 @@ vs_status vs_nn_forward(vs_nn* n, const uint16_t* x, const vs_nn_images* imgs, f
         h = n->hid[l];
     }
     const int ci = n->spec.cin[L - 1], co = n->spec.cout[L - 1];
+    // the caller's copy straight from the last layer where its stores may be
+    // 16 bytes wide
+    const bool both = pred && (uintptr_t)pred % 16 == 0;
     if (e == hipSuccess)
         e = nn::conv3x3(h, ci, n->w16[L - 1], n->params + n->off[L - 1] + (size_t)co * 9 * ci, n->pred, co, T,
-                        nn::CONV_F32, n->spec.alpha, s);
-    if (e == hipSuccess && pred)
+                        nn::CONV_F32, n->spec.alpha, s, both ? pred : nullptr);
+    if (e == hipSuccess && pred && !both)
         e = hipMemcpyAsync(pred, n->pred, (size_t)npix * co * 4, hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess) return st(e);
     n->x = x;
@@ -274,8 +275,8 @@ vs_status vs_nn_backward(vs_nn* n, const float* label, float* loss_sum, void* st
         const uint16_t* in = l == 0 ? n->x : n->hid[l - 1];
         e = nn::conv3x3_wgrad(in, ci, n->dz[cur], co, n->T, n->scratch, n->grads + n->off[l], s);
         if (e != hipSuccess || l == 0) break;
-        e = nn::conv3x3(n->dz[cur], co, n->wf16[l], nullptr, n->dh, ci, n->T, nn::CONV_LINEAR, n->spec.alpha, s);
-        if (e == hipSuccess) e = nn::lrelu_bwd(n->dh, n->hid[l - 1], n->dz[cur ^ 1], P * ci, n->spec.alpha, s);
+        e = nn::conv3x3(n->dz[cur], co, n->wf16[l], nullptr, n->dz[cur ^ 1], ci, n->T, nn::CONV_DGRAD, n->spec.alpha, s,
+                        n->hid[l - 1]);
         cur ^= 1;
     }
     return st(e);
@@ -287,9 +288,18 @@ vs_status vs_nn_adam_step(vs_nn* n, float lr, float b1, float b2, float eps, voi
         return VS_E_INVAL;
     hipStream_t s = (hipStream_t)stream;
     n->step += 1;
-    hipError_t e = nn::adam(n->params, n->m, n->v, n->grads, nullptr, (long)n->n_params, lr, b1, b2, eps, n->step, s);
-    if (e == hipSuccess) e = refresh(n, s);
-    return st(e);
+    static_assert(VS_NN_MAX_LAYERS <= nn::MAXN, "layer table");
+    nn::NetTable N = {};
+    N.n = n->L;
+    for (int l = 0; l < n->L; ++l) {
+        N.off[l] = (int32_t)n->off[l];
+        N.cin[l] = n->spec.cin[l];
+        N.cout[l] = n->spec.cout[l];
+        N.w16[l] = n->w16[l];
+        N.wf16[l] = n->wf16[l];
+    }
+    N.off[n->L] = (int32_t)n->off[n->L];
+    return st(nn::adam_net(N, n->params, n->m, n->v, n->grads, lr, b1, b2, eps, n->step, s));
 }
 
 vs_status vs_nn_params(vs_nn* n, float* params, float* grads, size_t* count, void* stream)

@@ -177,6 +177,45 @@ def test_conv_backward_matches_oracle(cin, cout):
     assert e_dx <= 1e-5 and e_dw <= 1e-5 and e_db <= 1e-5
 
 
+@pytest.mark.parametrize("cin,cout", [(16, 32), (32, 32), (32, 16)])
+@pytest.mark.parametrize("sizes", [[(1, 1)], [(1, 300), (300, 1)], [(129, 2), (16, 17), (4, 64)], [(16, 16)] * 3,
+                                   [(700, 400)]])
+def test_weight_gradient_at_unit_edges(cin, cout, sizes):
+    """units of 256 pixels that end within, at and past a row's and an image's end,
+    more units than resident blocks, activations and scratch at their types' own
+    alignment: every sum within the worst-case bound of an FP32 sum of its n terms,
+    n u / (1 - n u) * sum |x dz|, and the same bits from a second call"""
+    rng = np.random.default_rng(11 * cin + cout + len(sizes))
+    P = sum(h * w for h, w in sizes)
+    x, dz = to_bf16(rng.normal(size=(P, cin))), to_bf16(rng.normal(size=(P, cout)))
+    imgs = V.nn_images(sizes)
+    say(f"[wgrad {cin}->{cout}] {sizes}")
+    xd = torch.empty(P * cin + 1, dtype=torch.int16, device="cuda:0")[1:]
+    zd = torch.empty(P * cout + 1, dtype=torch.int16, device="cuda:0")[1:]
+    xd.copy_(dev(x).reshape(-1))
+    zd.copy_(dev(dz).reshape(-1))
+    nbytes = V.lib().vs_nn_wgrad_scratch_bytes(cin, cout, C.byref(imgs))
+    scratch = torch.empty(nbytes // 4 + 1, dtype=torch.float32, device="cuda:0")[1:]
+    outs = []
+    for _ in range(2):
+        dwb = torch.empty(cout * 9 * cin + cout, dtype=torch.float32, device="cuda:0")
+        V.check(V.lib().vs_nn_conv3x3_wgrad(C.c_void_p(xd.data_ptr()), cin, C.c_void_p(zd.data_ptr()), cout,
+                                            C.byref(imgs), C.c_void_p(scratch.data_ptr()), nbytes,
+                                            C.c_void_p(dwb.data_ptr()), None), "wgrad")
+        outs.append(dwb.cpu().numpy().astype(np.float64))
+    np.testing.assert_array_equal(outs[0], outs[1])
+    ref, mag, off = np.zeros(cout * 9 * cin + cout), np.zeros(cout * 9 * cin + cout), 0
+    for h, w in sizes:
+        xi = from_bf16(x)[off:off + h * w].reshape(1, h, w, cin)
+        gi = from_bf16(dz)[off:off + h * w].reshape(1, h, w, cout)
+        off += h * w
+        for acc, a, g in ((ref, xi, gi), (mag, np.abs(xi), np.abs(gi))):
+            dw, db = O.conv3x3_bwd_weight(a, g)
+            acc += np.concatenate([dw.reshape(-1), db.reshape(-1)])
+    u = 2.0 ** -24
+    assert (np.abs(outs[0] - ref) <= (P + 1) * u / (1 - (P + 1) * u) * mag).all()
+
+
 def test_loss_lrelu_adam_kernels():
     rng = np.random.default_rng(5)
     P = 1000
