@@ -258,8 +258,8 @@ vs_status vs_get_timing(vs_ctx* c, double ms[6], uint32_t* frames);
 /* Flow-kernel variant of one pyramid level: 0 = generic kernel (16 x 16
  * pixel tiles, any radius), 1, 2, 3 or 4 = the 9x9-window kernel (radius 4)
  * with that many vertically adjacent pixels per thread; + 8 (VS_FLOW_ALT):
- * the previous gradient row kept in a second register set instead of read
- * again from LDS; + 16 (VS_FLOW_INBLOCK): pixels whose displacement leaves
+ * accepted, the same kernel (the previous gradient row is always kept in
+ * registers); + 16 (VS_FLOW_INBLOCK): pixels whose displacement leaves
  * the staged tile are finished by their own block at its end instead of by a
  * tail launch.  Results are identical for every variant; only speed differs.
  * vs_create picks one per level; the autotuner below measures them. */

@@ -193,9 +193,15 @@ __global__ __launch_bounds__(256) void k_lk(const Batch B, int l)
 //  - per pixel each row of the moving image is interpolated along x once per
 //    step and used at once by the two window rows it serves: as the top row
 //    of window row k (sums SA) and the bottom row of window row k - 1 (SB).
-// ALT keeps the previous gradient row in a second register set (the row
-// loop unrolled by two, no copies); without it that row is read again from
-// LDS (fewer registers).
+//  - two gradient rows sit in registers in turn (lk_rhs), so each is read from
+//    LDS once per step.
+// Bound at 4 pixels per thread by LDS reads (154 words per pixel and step, the
+// LDS active 84 % of the time) and FP32 VALU together (wavefront instructions
+// 2 cycles each where all operands are vector registers, 4 otherwise); 124 - 128
+// VGPRs and 37.6 KB of LDS, 4 blocks per compute unit.  4 x 1080p ring, level 0
+// (4 px per thread) 289 -> 272 us, level 1 (3) 99 -> 90 us, one 256 x 1080 pair's
+// level 0 (2) 74 -> 62 us against rows in a loop with their reads where they are
+// used and two division operators per update.
 // INBLOCK: the block finishes its own deferred pixels at its end instead of
 // queueing them for the tail kernel: after a barrier each wavefront takes its
 // deferred pixels four at a time, one per 16-lane group (lk_tail_group, the
@@ -209,6 +215,9 @@ __global__ __launch_bounds__(256) void k_lk(const Batch B, int l)
 // in order, the lane of each row adding its taps to the partial sums it
 // received from the lane of the row above and handing them on, so each sum is
 // the same row-major sequence of fused multiply-adds as in the staged kernel.
+// LDS floats of the forms with several lanes per pixel
+constexpr int LK_SPLIT_LDS = 16 * 256;
+
 constexpr int LK_TAIL_G = 16;
 constexpr int LK_TAIL_M = 3;
 constexpr int LK_TAIL_SW = 2 * LK_R_MAX + 2 + 2 * LK_TAIL_M;   // staged window side (16)
@@ -223,58 +232,204 @@ __device__ __forceinline__ float row_shr1(float v)
 __device__ __forceinline__ void lk_tail_group(const DevPlan* __restrict__ Pl, int l, int f, int x, int y, int it0,
                                            float ux, float uy, int sub, float* mv);
 
-// Tile row t of a Gauss-Newton step: pixel q interpolates its moving-image row
-// k = t - q along x (g_base: this thread's gradient column 0 on the wavefront's
-// first tile row); cur receives gradient row t (window row k of pixel q, sums
-// SA), prev holds row t - 1 (window row k - 1, sums SB), read again from LDS
-// when LOAD_PREV.
-template <int P, int TIW, int MWP, bool LOAD_PREV>
-__device__ __forceinline__ void lk_rhs_row(int t, const float2* __restrict__ g_base, const float* __restrict__ sM,
-                                           const int (&mb)[P], const float (&fx)[P],
-                                           float2 (&cur)[2 * LK_R_MAX + 1], float2 (&prev)[2 * LK_R_MAX + 1],
-                                           float (&sau)[P], float (&sav)[P], float (&sbu)[P], float (&sbv)[P])
+// In-block finishing: the wavefront's deferred pixels (def, in row y of the tile
+// from column x0, S lanes per pixel holding the same flow (ux, uy) and step it0),
+// four at a time, one per 16-lane group, the windows in s_lds.  Called by whole
+// wavefronts after a barrier.
+template <int S>
+__device__ __forceinline__ void lk_finish(const DevPlan* __restrict__ Pl, int l, int f, int x0, int y, bool def,
+                                          float ux, float uy, int it0, float* s_lds)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    float* const win = s_lds + (wv * 4 + (lane >> 4)) * (LK_TAIL_SW * LK_TAIL_SW);
+    unsigned long long m = __ballot(def && lane % S == 0);
+    while (m != 0ull) {   // the same for the whole wavefront
+        // the next (up to) 4 deferred pixels, one per 16-lane group
+        int src = -1;
+        for (int g = 0; g < 4 && m != 0ull; ++g) {
+            const int s = __builtin_ctzll(m);
+            m &= m - 1ull;
+            if ((lane >> 4) == g) src = s;
+        }
+        const int s0 = src < 0 ? 0 : src;
+        const float pux = __shfl(ux, s0, 64), puy = __shfl(uy, s0, 64);
+        const int pit = __shfl(it0, s0, 64);
+        if (src >= 0) lk_tail_group(Pl, l, f, x0 + src / S, y, pit, pux, puy, lane & 15, win);
+    }
+}
+
+// Two quotients by one divisor, correctly rounded (the same bits as the division
+// operator): the reciprocal y of d, itself correctly rounded, then for each
+// numerator q = n y and twice the remainder step q + (n - q d) y, the second from a
+// quotient within one unit in the last place, which rounds correctly (Markstein,
+// "Computation of elementary functions on the IBM RISC System/6000", 1990).
+// No intermediate leaves the normal range for d in [DIV_LO, DIV_HI] and numerators
+// that are 0 or between 2^-60 and 2^60 in magnitude.  The remainder is formed
+// negated, so that zeros keep their sign.  20 plain multiplications and additions
+// where the two operators take 40 instructions, half of them at the half rate.
+constexpr float DIV_LO = 0x1p-40f, DIV_HI = 0x1p60f;
+
+__device__ __forceinline__ float div_rcp(float d)
+{
+    const float y = __builtin_amdgcn_rcpf(d);
+    return __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
+}
+
+__device__ __forceinline__ bool div_ok(float n0, float n1)
+{
+    const float a = fabsf(n0), b = fabsf(n1);
+    return fmaxf(a, b) <= 0x1p60f && (a >= 0x1p-60f || a == 0.0f) && (b >= 0x1p-60f || b == 0.0f);
+}
+
+__device__ __forceinline__ float div_by(float n, float d, float y)
+{
+    float q = n * y;
+    q = __builtin_fmaf(-__builtin_fmaf(d, q, -n), y, q);
+    return __builtin_fmaf(-__builtin_fmaf(d, q, -n), y, q);
+}
+
+// A Gauss-Newton step's rows as a list of units in order: tile row t, then pixel
+// q; pixel q interpolates its moving-image row k = t - q along x and uses it at
+// once with gradient row t (window row k, sums SA) and t - 1 (window row k - 1,
+// sums SB).
+template <int P>
+struct LkUnits {
+    static constexpr int N = P * (2 * LK_R_MAX + 2);
+    int t[N + 1], q[N + 1];
+    constexpr LkUnits() : t(), q()
+    {
+        int n = 0;
+        for (int tt = 0; tt < P + 2 * LK_R_MAX + 1; ++tt)
+            for (int qq = 0; qq < P; ++qq)
+                if (tt - qq >= 0 && tt - qq <= 2 * LK_R_MAX + 1) {
+                    t[n] = tt;
+                    q[n] = qq;
+                    ++n;
+                }
+        t[n] = -1;
+        q[n] = 0;
+    }
+};
+
+// LDS by byte address
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) const float lds_f32;
+typedef __attribute__((address_space(3))) const f32x2 lds_f32x2;
+
+__device__ __forceinline__ uint32_t lds_addr(const void* p)
+{
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
+}
+
+template <typename T>
+__device__ __forceinline__ T* lds_at(uint32_t a)
+{
+    return (T*)(uintptr_t)a;
+}
+
+// The sums of one step (ga: the LDS address of this thread's gradient column 0 on
+// the wavefront's first tile row; ma: of the moving image at the pixels' window
+// rows 0, column 0).  Every unit is unrolled, and its LDS reads are issued a unit
+// ahead: the next unit's moving row before this unit's arithmetic, the next
+// gradient row between the last unit's SB sums, the last use of the row it
+// replaces, and its SA sums.  A row's address is formed once and kept opaque, so
+// that its reads take it with immediate offsets (the paired reads' offsets span
+// 1 KB only: folded into one base, each read costs an addition of its own).
+template <int P, int TIW, int MWP>
+__device__ __forceinline__ void lk_rhs(uint32_t ga, const uint32_t (&ma)[P], const float (&fx)[P], float (&sau)[P],
+                                       float (&sav)[P], float (&sbu)[P], float (&sbv)[P])
 {
     constexpr int R = LK_R_MAX, NW = 2 * R + 1, NJ = P + 2 * R;
-    if (t < NJ) {
+    constexpr LkUnits<P> U;
+    f32x2 g[2][NW];
+    float m[2][NW + 1];
 #pragma unroll
-        for (int c = 0; c < NW; ++c) cur[c] = g_base[t * TIW + c];
-    }
-    if (LOAD_PREV && t >= 1) {
+    for (int c = 0; c < NW; ++c) g[0][c] = lds_at<lds_f32x2>(ga)[c];
 #pragma unroll
-        for (int c = 0; c < NW; ++c) prev[c] = g_base[(t - 1) * TIW + c];
-    }
+    for (int c = 0; c <= NW; ++c) m[0][c] = lds_at<lds_f32>(ma[0])[c];
 #pragma unroll
-    for (int q = 0; q < P; ++q) {
-        const int k = t - q;
-        if (k < 0 || k > 2 * R + 1) continue;
-        const float* m = sM + mb[q] + k * MWP;
+    for (int u = 0; u < U.N; ++u) {
+        const int t = U.t[u], q = U.q[u], k = t - q;
+        if (u + 1 < U.N) {
+            uint32_t mn = ma[U.q[u + 1]] + (uint32_t)((U.t[u + 1] - U.q[u + 1]) * MWP * 4);
+            asm volatile("" : "+v"(mn));
+#pragma unroll
+            for (int c = 0; c <= NW; ++c) m[(u + 1) & 1][c] = lds_at<lds_f32>(mn)[c];
+        }
+        __builtin_amdgcn_sched_barrier(0);
         float hr[NW];
-        float v0 = m[0];
 #pragma unroll
-        for (int c = 0; c < NW; ++c) {
-            const float v1 = m[c + 1];
-            hr[c] = __builtin_fmaf(fx[q], v1 - v0, v0);
-            v0 = v1;
+        for (int c = 0; c < NW; ++c) hr[c] = __builtin_fmaf(fx[q], m[u & 1][c + 1] - m[u & 1][c], m[u & 1][c]);
+        if (k >= 1) {
+#pragma unroll
+            for (int c = 0; c < NW; ++c) {
+                sbu[q] = __builtin_fmaf(g[(t + 1) & 1][c].x, hr[c], sbu[q]);
+                sbv[q] = __builtin_fmaf(g[(t + 1) & 1][c].y, hr[c], sbv[q]);
+            }
+        }
+        if (U.t[u + 1] == t + 1 && t + 1 < NJ) {
+            __builtin_amdgcn_sched_barrier(0);
+            ga += (uint32_t)(TIW * 8);
+            asm volatile("" : "+v"(ga));
+#pragma unroll
+            for (int c = 0; c < NW; ++c) g[(t + 1) & 1][c] = lds_at<lds_f32x2>(ga)[c];
+            __builtin_amdgcn_sched_barrier(0);
         }
         if (k <= 2 * R) {
 #pragma unroll
             for (int c = 0; c < NW; ++c) {
-                sau[q] = __builtin_fmaf(cur[c].x, hr[c], sau[q]);
-                sav[q] = __builtin_fmaf(cur[c].y, hr[c], sav[q]);
+                sau[q] = __builtin_fmaf(g[t & 1][c].x, hr[c], sau[q]);
+                sav[q] = __builtin_fmaf(g[t & 1][c].y, hr[c], sav[q]);
             }
         }
-        if (k >= 1) {
+        // the unit's sums are due here (otherwise all of them sink to where the
+        // update reads them, with every row held in registers until then)
+        asm volatile("" : "+v"(sau[q]), "+v"(sav[q]), "+v"(sbu[q]), "+v"(sbv[q]));
+    }
+}
+
+// The same sums of one pixel with its gradient window in registers (G).
+template <int MWP>
+__device__ __forceinline__ void lk_rhs_held(const f32x2 (&G)[2 * LK_R_MAX + 1][2 * LK_R_MAX + 1], uint32_t ma, float fx,
+                                            float& sau, float& sav, float& sbu, float& sbv)
+{
+    constexpr int NW = 2 * LK_R_MAX + 1;
 #pragma unroll
-            for (int c = 0; c < NW; ++c) {
-                sbu[q] = __builtin_fmaf(prev[c].x, hr[c], sbu[q]);
-                sbv[q] = __builtin_fmaf(prev[c].y, hr[c], sbv[q]);
+    for (int k = 0; k <= NW; ++k) {
+        float hr[NW], v0 = lds_at<lds_f32>(ma)[k * MWP];
+#pragma unroll
+        for (int c = 0; c < NW; ++c) {
+            const float v1 = lds_at<lds_f32>(ma)[k * MWP + c + 1];
+            hr[c] = __builtin_fmaf(fx, v1 - v0, v0);
+            v0 = v1;
+        }
+#pragma unroll
+        for (int c = 0; c < NW; ++c) {
+            if (k < NW) {
+                sau = __builtin_fmaf(G[k < NW ? k : 0][c].x, hr[c], sau);
+                sav = __builtin_fmaf(G[k < NW ? k : 0][c].y, hr[c], sav);
+            }
+            if (k > 0) {
+                sbu = __builtin_fmaf(G[k > 0 ? k - 1 : 0][c].x, hr[c], sbu);
+                sbv = __builtin_fmaf(G[k > 0 ? k - 1 : 0][c].y, hr[c], sbv);
             }
         }
     }
 }
 
-template <int P, bool INBLOCK, bool ALT>
-__device__ __forceinline__ void lk_w9_body(const DevPlan* __restrict__ Pl, const int bid, int l)
+// the staged tiles of lk_w9_body in floats, in one buffer: with INBLOCK its
+// first 16 KB hold the deferred pixels' moving windows after the steps (4 per
+// wavefront)
+constexpr int lk_w9_lds(int P)
+{
+    const int R = LK_R_MAX, tiw = LKW_TX + 2 * R, tih = 4 * P + 2 * R, hm = R + LK_D + 1;
+    const int n = tih * tiw * 2 + (tih + 2) * (tiw + 2) + (4 * P + 2 * hm) * ((LKW_TX + 2 * hm + 31) / 32 * 32);
+    return std::max(n, 16 * LK_TAIL_SW * LK_TAIL_SW);
+}
+
+// HOLD (1 pixel per thread): the gradient window in registers through the steps
+template <int P, bool INBLOCK, bool HOLD>
+__device__ __forceinline__ void lk_w9_body(const DevPlan* __restrict__ Pl, const int bid, int l, float* s_lds)
 {
     constexpr int R = LK_R_MAX, NW = 2 * R + 1;
     constexpr int TX = LKW_TX, TY = 4 * P;
@@ -285,12 +440,8 @@ __device__ __forceinline__ void lk_w9_body(const DevPlan* __restrict__ Pl, const
     // moving-tile row pitch: a multiple of the 32 LDS banks, so lanes whose
     // displacements put them one row apart read distinct banks
     constexpr int MWP = (MW + 31) / 32 * 32;
-    // the staged tiles in one buffer: with INBLOCK its first 16 KB hold the
-    // deferred pixels' moving windows after the steps (4 per wavefront)
     constexpr int NGF = TIH * TIW * 2, NTF = TSH * TSW, NMF = MH * MWP;   // floats
-    constexpr int NWF = 16 * LK_TAIL_SW * LK_TAIL_SW;
-    constexpr int NBUF = NGF + NTF + NMF > NWF ? NGF + NTF + NMF : NWF;
-    __shared__ __align__(16) float s_lds[NBUF];
+    static_assert(NGF + NTF + NMF <= lk_w9_lds(P), "the tiles fit");
     float2* const sG = reinterpret_cast<float2*>(s_lds);
     float* const sT = s_lds + NGF;
     float* const sM = s_lds + NGF + NTF;
@@ -395,13 +546,16 @@ __device__ __forceinline__ void lk_w9_body(const DevPlan* __restrict__ Pl, const
     __syncthreads();
 
     const int ncx = min(x + R, w - 1) - max(x - R, 0) + 1;
-    float ux[P], uy[P], g00[P], g01[P], g11[P], cu[P], cv[P], det[P];
+    float ux[P], uy[P], g00[P], g01[P], g11[P], cu[P], cv[P];
     bool act[P];
-    int dit[P];   // step at which the pixel was deferred (-1: not deferred)
+    // deferred pixels: cu then holds the step (its bits as an int; the tail forms its
+    // own sums); divf: det lies where div_by may divide
+    bool def[P], divf[P];
 #pragma unroll
     for (int q = 0; q < P; ++q) {
         act[q] = x < w && yb + q < h && nd[q] != 0u;
-        dit[q] = -1;
+        def[q] = false;
+        divf[q] = false;
         ux[q] = 0.0f;
         uy[q] = 0.0f;
         if (has_coarse && act[q]) {
@@ -460,68 +614,72 @@ __device__ __forceinline__ void lk_w9_body(const DevPlan* __restrict__ Pl, const
             const float reg = act[q] ? Pl->lk_lambda * (float)(ncy * ncx) : 1.0f;
             g00[q] = g00[q] + reg;
             g11[q] = g11[q] + reg;
-            det[q] = g00[q] * g11[q] - g01[q] * g01[q];
+            const float det = g00[q] * g11[q] - g01[q] * g01[q];
+            divf[q] = det >= DIV_LO && det <= DIV_HI;
         }
         const int iters = Pl->lk_iters;
+        f32x2 G[NW][NW];
+        if (HOLD) {
+            static_assert(!HOLD || P == 1, "one window");
+#pragma unroll
+            for (int k = 0; k < NW; ++k)
+#pragma unroll
+                for (int c = 0; c < NW; ++c) G[k][c] = f32x2{g_base[k * TIW + c].x, g_base[k * TIW + c].y};
+        }
+        const uint32_t ga0 = lds_addr(g_base), ma0 = lds_addr(sM + (wv * P - R + HM) * MWP + lane - R + HM);
         for (int it = 0; it < iters; ++it) {
-            float fx[P], fy[P], sau[P], sav[P], sbu[P], sbv[P];
-            int mb[P];
+            float fx[P], sau[P], sav[P], sbu[P], sbv[P];
+            uint32_t mb[P];
 #pragma unroll
             for (int q = 0; q < P; ++q) {
                 const float flx = floorf(ux[q]), fly = floorf(uy[q]);
-                int ox = (int)flx, oy = (int)fly;
                 fx[q] = ux[q] - flx;
-                fy[q] = uy[q] - fly;
                 sau[q] = 0.0f;
                 sav[q] = 0.0f;
                 sbu[q] = 0.0f;
                 sbv[q] = 0.0f;
-                if (act[q] && !(ox >= -(LK_D + 1) && ox <= LK_D && oy >= -(LK_D + 1) && oy <= LK_D)) {
+                // -(LK_D + 1) <= floor <= LK_D in both axes (a NaN stays and runs through)
+                const bool out = fmaxf(fabsf(flx + 0.5f), fabsf(fly + 0.5f)) > (float)LK_D + 0.5f;
+                if (act[q] && out) {
                     // the displacement leaves the staged tile: the pixel, with its state
                     // at the start of this step (kept from here on), goes to the tail
-                    dit[q] = it;
+                    def[q] = true;
+                    cu[q] = __int_as_float(it);
                     act[q] = false;
                 }
-                if (!act[q]) {
-                    ox = 0;
-                    oy = 0;
-                }
-                mb[q] = (wv * P + q - R + HM + oy) * MWP + (lane - R + HM + ox);
+                const int off = act[q] ? (int)__builtin_fmaf(fly, 4.0f * MWP, 4.0f * flx) : 0;
+                mb[q] = ma0 + (uint32_t)(off + q * MWP * 4);
             }
-            // tile rows t = 0 .. P + 2R: moving-image row t - q of pixel q
-            constexpr int NT = P + 2 * R + 1;
-            float2 gA[NW], gB[NW];
-            if (ALT && P == 1 && INBLOCK) {
-                // the levels this form is for hold about one wavefront per SIMD: the
-                // rows unrolled, so the next rows' LDS reads are in flight while a
-                // row computes (216 VGPRs, occupancy they do not need)
-#pragma unroll
-                for (int t = 0; t + 1 < NT; t += 2) {
-                    lk_rhs_row<P, TIW, MWP, false>(t, g_base, sM, mb, fx, gA, gB, sau, sav, sbu, sbv);
-                    lk_rhs_row<P, TIW, MWP, false>(t + 1, g_base, sM, mb, fx, gB, gA, sau, sav, sbu, sbv);
-                }
-                if (NT % 2) lk_rhs_row<P, TIW, MWP, false>(NT - 1, g_base, sM, mb, fx, gA, gB, sau, sav, sbu, sbv);
-            } else if (ALT) {
-#pragma unroll 1
-                for (int t = 0; t + 1 < NT; t += 2) {
-                    lk_rhs_row<P, TIW, MWP, false>(t, g_base, sM, mb, fx, gA, gB, sau, sav, sbu, sbv);
-                    lk_rhs_row<P, TIW, MWP, false>(t + 1, g_base, sM, mb, fx, gB, gA, sau, sav, sbu, sbv);
-                }
-                if (NT % 2) lk_rhs_row<P, TIW, MWP, false>(NT - 1, g_base, sM, mb, fx, gA, gB, sau, sav, sbu, sbv);
+            // (the gradients do not change from step to step; the opaque address
+            // keeps the compiler from holding all of them in registers)
+            uint32_t ga = ga0;
+            if (HOLD) {
+                lk_rhs_held<MWP>(G, mb[0], fx[0], sau[0], sav[0], sbu[0], sbv[0]);
             } else {
-#pragma unroll 1
-                for (int t = 0; t < NT; ++t)
-                    lk_rhs_row<P, TIW, MWP, true>(t, g_base, sM, mb, fx, gA, gB, sau, sav, sbu, sbv);
+                asm volatile("" : "+v"(ga));
+                lk_rhs<P, TIW, MWP>(ga, mb, fx, sau, sav, sbu, sbv);
             }
 #pragma unroll
             for (int q = 0; q < P; ++q) {
-                if (!act[q]) continue;
-                const float bu = __builtin_fmaf(fy[q], sbu[q] - sau[q], sau[q]) - cu[q];
-                const float bv = __builtin_fmaf(fy[q], sbv[q] - sav[q], sav[q]) - cv[q];
-                const float du = (g01[q] * bv - g11[q] * bu) / det[q];
-                const float dv = (g01[q] * bu - g00[q] * bv) / det[q];
-                ux[q] = ux[q] + du;
-                uy[q] = uy[q] + dv;
+                // formed again each step rather than held through the rows: the
+                // registers decide how many wavefronts are resident
+                asm volatile("" : "+v"(uy[q]), "+v"(g00[q]), "+v"(g01[q]), "+v"(g11[q]));
+                const float fy = uy[q] - floorf(uy[q]);
+                const float det = g00[q] * g11[q] - g01[q] * g01[q];
+                const float bu = __builtin_fmaf(fy, sbu[q] - sau[q], sau[q]) - cu[q];
+                const float bv = __builtin_fmaf(fy, sbv[q] - sav[q], sav[q]) - cv[q];
+                const float nu = g01[q] * bv - g11[q] * bu, nv = g01[q] * bu - g00[q] * bv;
+                float du, dv;
+                if (__any(act[q] && !(divf[q] && div_ok(nu, nv)))) {
+                    du = nu / det;
+                    dv = nv / det;
+                } else {
+                    const float y = div_rcp(det);
+                    du = div_by(nu, det, y);
+                    dv = div_by(nv, det, y);
+                }
+                ux[q] = act[q] ? ux[q] + du : ux[q];
+                uy[q] = act[q] ? uy[q] + dv : uy[q];
             }
         }
 #pragma unroll
@@ -530,25 +688,9 @@ __device__ __forceinline__ void lk_w9_body(const DevPlan* __restrict__ Pl, const
     }   // wave_live
     if (INBLOCK) {
         __syncthreads();   // every wavefront is done with the staged tiles
-        float* const win = s_lds + (wv * 4 + (lane >> 4)) * (LK_TAIL_SW * LK_TAIL_SW);
-        const int sub = lane & 15;
 #pragma unroll
-        for (int q = 0; q < P; ++q) {
-            unsigned long long m = __ballot(dit[q] >= 0);
-            while (m != 0ull) {   // the same for the whole wavefront
-                // the next (up to) 4 deferred lanes, one per 16-lane group
-                int src = -1;
-                for (int g = 0; g < 4 && m != 0ull; ++g) {
-                    const int s = __builtin_ctzll(m);
-                    m &= m - 1ull;
-                    if ((lane >> 4) == g) src = s;
-                }
-                const int s0 = src < 0 ? 0 : src;
-                const float pux = __shfl(ux[q], s0, 64), puy = __shfl(uy[q], s0, 64);
-                const int pit = __shfl(dit[q], s0, 64);
-                if (src >= 0) lk_tail_group(Pl, l, f, x0 + src, yb + q, pit, pux, puy, sub, win);
-            }
-        }
+        for (int q = 0; q < P; ++q)
+            lk_finish<1>(Pl, l, f, x0, yb + q, def[q], ux[q], uy[q], __float_as_int(cu[q]), s_lds);
     } else {
         // queue the deferred pixels for the tail kernel: one reservation per
         // wavefront, after the steps (a reservation returns only after a round
@@ -558,7 +700,7 @@ __device__ __forceinline__ void lk_w9_body(const DevPlan* __restrict__ Pl, const
         uint32_t tot = 0;
 #pragma unroll
         for (int q = 0; q < P; ++q) {
-            mq[q] = __ballot(dit[q] >= 0);
+            mq[q] = __ballot(def[q]);
             tot += (uint32_t)__popcll(mq[q]);
         }
         if (tot != 0u) {
@@ -567,11 +709,11 @@ __device__ __forceinline__ void lk_w9_body(const DevPlan* __restrict__ Pl, const
             base = (uint32_t)__shfl((int)base, 0, 64);
 #pragma unroll
             for (int q = 0; q < P; ++q) {
-                if (dit[q] >= 0) {
+                if (def[q]) {
                     const uint32_t slot =
                         base + __builtin_amdgcn_mbcnt_hi((uint32_t)(mq[q] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mq[q], 0u));
                     if (slot < (uint32_t)Pl->lk_qcap[l])
-                        Pl->lk_queue[l][slot] = make_uint4((uint32_t)f | ((uint32_t)dit[q] << 8),
+                        Pl->lk_queue[l][slot] = make_uint4((uint32_t)f | (__float_as_uint(cu[q]) << 8),
                                                            (uint32_t)x | ((uint32_t)(yb + q) << 16),
                                                            __float_as_uint(ux[q]), __float_as_uint(uy[q]));
                 }
@@ -583,15 +725,199 @@ __device__ __forceinline__ void lk_w9_body(const DevPlan* __restrict__ Pl, const
 
 // the 4-pixel forms held to 128 VGPRs (4 blocks per compute unit) also when
 // they finish their deferred pixels in-block
-template <int P, bool INBLOCK, bool ALT = false>
+template <int P, bool INBLOCK, bool HOLD = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == 4 && INBLOCK ? 4 : 1)))
 void k_lk_w9(const Batch B, int l)
 {
+    __shared__ __align__(16) float s_lds[lk_w9_lds(P)];
     int c;
     const int b = batch_block(B, blockIdx.x, c);
-    lk_w9_body<P, INBLOCK, ALT>(B.plan[c], b, l);
+    lk_w9_body<P, INBLOCK, HOLD>(B.plan[c], b, l, s_lds);
 }
 
+// the value of lane K of each 4 in all of them (DPP quad permutation)
+template <int K>
+__device__ __forceinline__ float quad_bcast(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), K * 0x55, 0xf, 0xf, true));
+}
+
+// Small levels: 4 lanes per pixel, a 16 x 4 pixel block tile.  A level of few pixels
+// runs at most about one wavefront per SIMD, which issues an instruction every 6
+// cycles whatever the unit could take: what counts is the instructions of one
+// wavefront, so a pixel's chains of sums are dealt out, one of SAu, SAv, SBu, SBv
+// per lane (243 instructions per step instead of 504; interpolated rows are formed
+// by each lane that uses them).  Every sum is the same row-major sequence as in
+// lk_w9_body, the update is done by all lanes of a pixel alike.  The gradients stay
+// in registers through the steps.  The moving rows' pitch puts the SA and the SB
+// lanes' rows in distinct banks.  8600 pixels: 10.7 us, 1 pixel per thread 14.0.
+__device__ __forceinline__ void lk_split_body(const DevPlan* __restrict__ Pl, const int bid, int l, float* s_lds)
+{
+    constexpr int R = LK_R_MAX, NW = 2 * R + 1;
+    constexpr int TX = LK_SPLIT_TX, TY = 4;
+    constexpr int TIW = TX + 2 * R, TIH = TY + 2 * R;       // gradient window positions
+    constexpr int TSW = TIW + 2, TSH = TIH + 2;             // template + gradient halo
+    constexpr int HM = R + LK_D + 1;                        // moving-image halo
+    constexpr int MW = TX + 2 * HM, MH = TY + 2 * HM;
+    constexpr int MWP = (MW + 15) / 32 * 32 + 16;           // 16 banks on from row to row
+    constexpr int NGF = TIH * TIW * 2, NTF = TSH * TSW;
+    static_assert(MWP >= MW && MW <= 64 && TSW <= 64, "a column per lane");
+    static_assert(NGF + NTF + MH * MWP <= LK_SPLIT_LDS && 16 * LK_TAIL_SW * LK_TAIL_SW <= LK_SPLIT_LDS, "the tiles fit");
+    float2* const sG = reinterpret_cast<float2*>(s_lds);
+    float* const sT = s_lds + NGF;
+    float* const sM = s_lds + NGF + NTF;
+
+    const int f = find_field(Pl->lk_off[l], 2 * Pl->n_pairs, bid);
+    const int p = f >> 1, dir = f & 1;
+    int x0, y0;
+    tile_origin(Pl, l, f, bid, TX, TY, x0, y0);
+    if (kept_by_surrogate(Pl, p)) return;         // the pair keeps the surrogate's flows
+    const int w = Pl->lw[p][l], h = Pl->lh[p][l];
+    const float* __restrict__ Tm = Pl->pyr[p][dir == 0 ? 0 : 1][l];
+    const float* __restrict__ Mv = Pl->pyr[p][dir == 0 ? 1 : 0][l];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int x = x0 + lane / 4, y = y0 + wv;
+    const int side = (lane >> 1) & 1;   // 0: sums SA, 1: SB
+    const int own = lane & 1;                               // 0: with Ix, 1: with Iy
+
+    // the pixel's flow-domain flag and coarse flows, then both tiles by rows, every
+    // load before the first LDS store
+    const bool in = x < w && y < h;
+    const uint32_t nd = Pl->need[p][l][(size_t)min(y, h - 1) * w + min(x, w - 1)];
+    float ux = 0.0f, uy = 0.0f;
+    float2 c00, c10, c01, c11;
+    float cfx = 0.0f, cfy = 0.0f;
+    const bool has_coarse = l + 1 < Pl->levels;
+    if (has_coarse) {
+        const int wc = Pl->lw[p][l + 1], hc = Pl->lh[p][l + 1];
+        const float2* __restrict__ uc = Pl->flow[p][dir][l + 1];
+        const float cx = clampf(__builtin_fmaf((float)x, 0.5f, -0.25f), 0.0f, (float)(wc - 1));
+        const float cy = clampf(__builtin_fmaf((float)y, 0.5f, -0.25f), 0.0f, (float)(hc - 1));
+        const float flx = floorf(cx), fly = floorf(cy);
+        const int xa = (int)flx, ya = (int)fly;
+        cfx = cx - flx;
+        cfy = cy - fly;
+        const int xb = xa + 1 < wc ? xa + 1 : wc - 1, yb = ya + 1 < hc ? ya + 1 : hc - 1;
+        c00 = uc[(size_t)ya * wc + xa];
+        c10 = uc[(size_t)ya * wc + xb];
+        c01 = uc[(size_t)yb * wc + xa];
+        c11 = uc[(size_t)yb * wc + xb];
+    }
+    constexpr int RT = (TSH + 3) / 4, RM = (MH + 3) / 4;
+    const int tc = clampi(x0 - R - 1 + lane, 0, w - 1), mc = clampi(x0 - HM + lane, 0, w - 1);
+    float vt[RT], vm[RM];
+#pragma unroll
+    for (int j = 0; j < RT; ++j) vt[j] = Tm[(size_t)clampi(y0 - R - 1 + wv + 4 * j, 0, h - 1) * w + tc];
+#pragma unroll
+    for (int j = 0; j < RM; ++j) vm[j] = Mv[(size_t)clampi(y0 - HM + wv + 4 * j, 0, h - 1) * w + mc];
+#pragma unroll
+    for (int j = 0; j < RT; ++j) {
+        const int r = wv + 4 * j;
+        if (r < TSH && lane < TSW) sT[r * TSW + lane] = vt[j];
+    }
+#pragma unroll
+    for (int j = 0; j < RM; ++j) {
+        const int r = wv + 4 * j;
+        if (r < MH && lane < MW) sM[r * MWP + lane] = vm[j];
+    }
+    __syncthreads();
+    for (int gy = wv; gy < TIH; gy += 4) {
+        if (lane < TIW) {
+            const int X = x0 - R + lane, Y = y0 - R + gy, c = (gy + 1) * TSW + lane + 1;
+            const bool ok = X >= 0 && X < w && Y >= 0 && Y < h;
+            sG[gy * TIW + lane] = make_float2(ok ? 0.5f * (sT[c + 1] - sT[c - 1]) : 0.0f,
+                                              ok ? 0.5f * (sT[c + TSW] - sT[c - TSW]) : 0.0f);
+        }
+    }
+    __syncthreads();
+
+    bool act = in && nd != 0u, def = false;
+    int it0 = 0;
+    if (__any(act)) {
+        if (has_coarse) {
+            float a = __builtin_fmaf(cfx, c10.x - c00.x, c00.x);
+            float b = __builtin_fmaf(cfx, c11.x - c01.x, c01.x);
+            ux = act ? 2.0f * __builtin_fmaf(cfy, b - a, a) : 0.0f;
+            a = __builtin_fmaf(cfx, c10.y - c00.y, c00.y);
+            b = __builtin_fmaf(cfx, c11.y - c01.y, c01.y);
+            uy = act ? 2.0f * __builtin_fmaf(cfy, b - a, a) : 0.0f;
+        }
+        // normal matrix and template term: the lanes of Ix sum g00, g01 and cu, those
+        // of Iy g11, g01 and cv
+        const float2* gp = sG + wv * TIW + lane / 4;
+        const float* ga = (const float*)gp + own;         // own gradient component, and the other
+        const float* gb = (const float*)gp + (own ^ 1);
+        const float* tp = sT + (wv + 1) * TSW + lane / 4 + 1;
+        float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
+#pragma unroll
+        for (int k = 0; k < NW; ++k)
+#pragma unroll
+            for (int c = 0; c < NW; ++c) {
+                const float a = ga[2 * (k * TIW + c)], b = gb[2 * (k * TIW + c)], tv = tp[k * TSW + c];
+                s0 = __builtin_fmaf(a, a, s0);
+                s1 = __builtin_fmaf(a, b, s1);
+                s2 = __builtin_fmaf(a, tv, s2);
+            }
+        const int ncx = min(x + R, w - 1) - max(x - R, 0) + 1, ncy = min(y + R, h - 1) - max(y - R, 0) + 1;
+        const float reg = act ? Pl->lk_lambda * (float)(ncy * ncx) : 1.0f;
+        const float g00 = quad_bcast<0>(s0) + reg, g11 = quad_bcast<1>(s0) + reg, g01 = quad_bcast<0>(s1);
+        const float cu = quad_bcast<0>(s2), cv = quad_bcast<1>(s2);
+        const float det = g00 * g11 - g01 * g01;
+        const bool divf = det >= DIV_LO && det <= DIV_HI;
+        const float y1 = div_rcp(det);
+        const int iters = Pl->lk_iters;
+        const float* mbase = sM + (wv - R + HM + side) * MWP + lane / 4 - R + HM;
+        for (int it = 0; it < iters; ++it) {
+            const float flx = floorf(ux), fly = floorf(uy);
+            const float fx = ux - flx, fy = uy - fly;
+            const bool out = fmaxf(fabsf(flx + 0.5f), fabsf(fly + 0.5f)) > (float)LK_D + 0.5f;
+            if (act && out) {   // as in lk_w9_body
+                def = true;
+                it0 = it;
+                act = false;
+            }
+            const float* m = mbase + (act ? (int)__builtin_fmaf(fly, (float)MWP, flx) : 0);
+            float acc = 0.0f;
+#pragma unroll
+            for (int k = 0; k < NW; ++k) {
+                float v0 = m[k * MWP];
+#pragma unroll
+                for (int c = 0; c < NW; ++c) {
+                    const float v1 = m[k * MWP + c + 1];
+                    acc = __builtin_fmaf(ga[2 * (k * TIW + c)], __builtin_fmaf(fx, v1 - v0, v0), acc);
+                    v0 = v1;
+                }
+            }
+            const float sau = quad_bcast<0>(acc), sav = quad_bcast<1>(acc);
+            const float sbu = quad_bcast<2>(acc), sbv = quad_bcast<3>(acc);
+            const float bu = __builtin_fmaf(fy, sbu - sau, sau) - cu;
+            const float bv = __builtin_fmaf(fy, sbv - sav, sav) - cv;
+            const float nu = g01 * bv - g11 * bu, nv = g01 * bu - g00 * bv;
+            float du, dv;
+            if (__any(act && !(divf && div_ok(nu, nv)))) {
+                du = nu / det;
+                dv = nv / det;
+            } else {
+                du = div_by(nu, det, y1);
+                dv = div_by(nv, det, y1);
+            }
+            ux = act ? ux + du : ux;
+            uy = act ? uy + dv : uy;
+        }
+        if (act && lane % 4 == 0) Pl->flow[p][dir][l][(size_t)y * w + x] = make_float2(ux, uy);
+    }
+    __syncthreads();   // every wavefront is done with the staged tiles
+    lk_finish<4>(Pl, l, f, x0, y, def, ux, uy, it0, s_lds);
+}
+
+// two wavefronts per SIMD at least
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_lk_split(const Batch B, int l)
+{
+    __shared__ __align__(16) float s_lds[LK_SPLIT_LDS];
+    int c;
+    const int b = batch_block(B, blockIdx.x, c);
+    lk_split_body(B.plan[c], b, l, s_lds);
+}
 
 // One deferred pixel finished by the 16 lanes of a group (lane sub holding
 // window row sub; mv: the group's 16 x 16 LDS window), from step it0 with the
@@ -811,7 +1137,7 @@ hipError_t launch_need(const DevPlan* dp, const DevPlan& hp, hipStream_t s)
 hipError_t launch_lk(const Group& g, int l, hipStream_t s)
 {
     // every context of a group runs the same flow-kernel variant at a level:
-    // 0 generic, else pixels per thread (1, 2, 4) plus 8 for alternating row registers
+    // 0 generic, else pixels per thread (1 - 4); + 8 runs the same kernel
     const int code = g.hp[0]->lk_P[l];
     for (int c = 1; c < g.n; ++c)
         if (g.hp[c]->lk_P[l] != code) return hipErrorInvalidValue;
@@ -823,25 +1149,29 @@ hipError_t launch_lk(const Group& g, int l, hipStream_t s)
     // (and variants that ask for it: no tail launch)
     bool inblock = (code & VS_FLOW_INBLOCK) != 0;
     for (int c = 0; c < g.n; ++c) inblock = inblock || g.hp[c]->flow_mode == VS_FLOW_SURROGATE_FALLBACK;
-    if (make_batch(g, B, [&](const DevPlan& h) { return plain(h) && l < h.levels ? h.lk_off[l][2 * h.n_pairs] : 0; })) {
+    // contexts whose level takes a small-level form launch by themselves
+    for (const int form : {LK_GENERAL, LK_HELD, LK_LANES4}) {
+        if (!make_batch(g, B, [&](const DevPlan& h) {
+                return plain(h) && l < h.levels && h.lk_form[l] == form ? h.lk_off[l][2 * h.n_pairs] : 0; }))
+            continue;
         const dim3 grid(B.off[B.n]);
-        switch (P * 2 + (inblock ? 1 : 0)) {
-        case 8: hipLaunchKernelGGL((k_lk_w9<4, false>), grid, dim3(256), 0, s, B, l); break;
-        case 9: hipLaunchKernelGGL((k_lk_w9<4, true>), grid, dim3(256), 0, s, B, l); break;
+        if (form == LK_LANES4) {
+            hipLaunchKernelGGL(k_lk_split, grid, dim3(256), 0, s, B, l);
+            continue;
+        }
+        if (form == LK_HELD) {
+            hipLaunchKernelGGL((k_lk_w9<1, true, true>), grid, dim3(256), 0, s, B, l);
+            continue;
+        }
+        switch ((P & 7) * 2 + (inblock ? 1 : 0)) {
+        case 2: hipLaunchKernelGGL((k_lk_w9<1, false>), grid, dim3(256), 0, s, B, l); break;
+        case 3: hipLaunchKernelGGL((k_lk_w9<1, true>), grid, dim3(256), 0, s, B, l); break;
         case 4: hipLaunchKernelGGL((k_lk_w9<2, false>), grid, dim3(256), 0, s, B, l); break;
         case 5: hipLaunchKernelGGL((k_lk_w9<2, true>), grid, dim3(256), 0, s, B, l); break;
         case 6: hipLaunchKernelGGL((k_lk_w9<3, false>), grid, dim3(256), 0, s, B, l); break;
         case 7: hipLaunchKernelGGL((k_lk_w9<3, true>), grid, dim3(256), 0, s, B, l); break;
-        case 22: hipLaunchKernelGGL((k_lk_w9<3, false, true>), grid, dim3(256), 0, s, B, l); break;
-        case 23: hipLaunchKernelGGL((k_lk_w9<3, true, true>), grid, dim3(256), 0, s, B, l); break;
-        case 2: hipLaunchKernelGGL((k_lk_w9<1, false>), grid, dim3(256), 0, s, B, l); break;
-        case 3: hipLaunchKernelGGL((k_lk_w9<1, true>), grid, dim3(256), 0, s, B, l); break;
-        case 24: hipLaunchKernelGGL((k_lk_w9<4, false, true>), grid, dim3(256), 0, s, B, l); break;
-        case 25: hipLaunchKernelGGL((k_lk_w9<4, true, true>), grid, dim3(256), 0, s, B, l); break;
-        case 20: hipLaunchKernelGGL((k_lk_w9<2, false, true>), grid, dim3(256), 0, s, B, l); break;
-        case 21: hipLaunchKernelGGL((k_lk_w9<2, true, true>), grid, dim3(256), 0, s, B, l); break;
-        case 18: hipLaunchKernelGGL((k_lk_w9<1, false, true>), grid, dim3(256), 0, s, B, l); break;
-        case 19: hipLaunchKernelGGL((k_lk_w9<1, true, true>), grid, dim3(256), 0, s, B, l); break;
+        case 8: hipLaunchKernelGGL((k_lk_w9<4, false>), grid, dim3(256), 0, s, B, l); break;
+        case 9: hipLaunchKernelGGL((k_lk_w9<4, true>), grid, dim3(256), 0, s, B, l); break;
         default: hipLaunchKernelGGL(k_lk, grid, dim3(256), 0, s, B, l); break;
         }
     }

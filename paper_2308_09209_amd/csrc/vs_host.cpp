@@ -210,16 +210,13 @@ void free_ctx(vs_ctx* c)
 // (n16) and the blocks the device holds at once (`resident`, four staged flow
 // blocks per compute unit).  A level with under two waves of resident blocks
 // at 1 pixel per thread takes P = 1 in the unrolled form that finishes its
-// (few) deferred pixels in-block: at about one wavefront per SIMD its rows'
-// LDS reads overlap, and no tail launch follows.  Otherwise the most pixels
+// (few) deferred pixels in-block (a form by itself at the smallest, lk_form_of):
+// no tail launch follows.  Otherwise the most pixels
 // per thread P (4, 3, 2, 1; n16 * 4 / P blocks) that still gives at least
 // one full wave of blocks, with a tail launch for the deferred pixels: over
 // a sequence, frames whose deferred pixels cluster in a few blocks make
 // in-block finishing end late (4x1080p p99 0.614 -> 0.638 ms, 8x4K mean
-// 3.556 -> 3.584 ms with it at the coarser levels).  Every P takes the form
-// that keeps the previous gradient row in registers: with the regrouped
-// right-hand side it costs no occupancy at P = 4 and saves the row's second
-// LDS read.
+// 3.556 -> 3.584 ms with it at the coarser levels).
 int default_lk_P(int n16, int resident)
 {
     if ((long)n16 * 4 < 2L * resident) return 1 + VS_FLOW_ALT + VS_FLOW_INBLOCK;
@@ -243,18 +240,46 @@ int lk_resident_blocks()
     return cached;
 }
 
-// Choose the flow-kernel variant of one level (0: generic 16x16 kernel;
-// 1, 2, 4: 9x9-window kernel with that many pixels per thread) and rebuild
-// that level's tile table; the caller re-uploads the plan.
-void set_lk_tiles(DevPlan& h, int l, int P)
+// Form of a level's flow kernel, from the pixels of its launch.  4 lanes per pixel
+// (two wavefronts per SIMD resident: 32768 pixels) 10.7 us at 8600 pixels and
+// 21 us at 34000, past them; the gradients held in registers (one wavefront per
+// SIMD: 65536 pixels) 14.6 us up to 45000 pixels and 16.8 at 67000, where the
+// general form takes 16.6 and 19.9; that takes 27.8 us at 132000, the held one 30.6.
+int lk_form_of(int P, long px)
 {
-    int tx = LK_T, ty = LK_T;
-    h.lk_P[l] = P;
-    h.lk_tiles[l] = nullptr;
-    if (P > 0) {
-        tx = LKW_TX;
-        ty = 4 * (P & 7);
+    if (P != 1 + VS_FLOW_INBLOCK && P != 1 + VS_FLOW_ALT + VS_FLOW_INBLOCK) return LK_GENERAL;
+    return px <= 30000 ? LK_LANES4 : px <= 75000 ? LK_HELD : LK_GENERAL;
+}
+
+// pixels of level l over every field
+long level_px(const DevPlan& h, int l)
+{
+    long n = 0;
+    for (int p = 0; p < h.n_pairs; ++p) n += 2L * h.lw[p][l] * h.lh[p][l];
+    return n;
+}
+
+// flow tile of a level's variant
+void lk_tile(const DevPlan& h, int l, int& tx, int& ty)
+{
+    tx = ty = LK_T;
+    if (h.lk_P[l] > 0) {
+        tx = h.lk_form[l] == LK_LANES4 ? LK_SPLIT_TX : LKW_TX;
+        ty = 4 * (h.lk_P[l] & 7);
     }
+}
+
+// Choose the flow-kernel variant of one level (0: generic 16x16 kernel;
+// 1 - 4: 9x9-window kernel with that many pixels per thread) and rebuild
+// that level's tile table; the caller re-uploads the plan.  px: the pixels of
+// the level's launch (a batch's: of all its contexts).
+void set_lk_tiles(DevPlan& h, int l, int P, long px)
+{
+    int tx, ty;
+    h.lk_P[l] = P;
+    h.lk_form[l] = lk_form_of(P, px);
+    h.lk_tiles[l] = nullptr;
+    lk_tile(h, l, tx, ty);
     h.lk_off[l][0] = 0;
     for (int f = 0; f < 2 * h.n_pairs; ++f) {
         const int p = f >> 1;
@@ -310,7 +335,8 @@ size_t lk_tile_cap(const DevPlan& h, int l)
     size_t n = 0;
     for (int f = 0; f < 2 * h.n_pairs; ++f) {
         const size_t w = (size_t)h.lw[f >> 1][l], hh = (size_t)h.lh[f >> 1][l];
-        n += std::max(((w + LKW_TX - 1) / LKW_TX) * ((hh + 3) / 4), ((w + LK_T - 1) / LK_T) * ((hh + LK_T - 1) / LK_T));
+        // (4 lanes per pixel: 16 x 4 px, the smallest tile)
+        n += ((w + LK_SPLIT_TX - 1) / LK_SPLIT_TX) * ((hh + 3) / 4);
     }
     return n;
 }
@@ -325,11 +351,8 @@ hipError_t band_tiles(vs_ctx* c, int l)
 {
     DevPlan& h = c->hp;
     if (!c->tiles) return hipSuccess;
-    int tx = LK_T, ty = LK_T;
-    if (h.lk_P[l] > 0) {
-        tx = LKW_TX;
-        ty = 4 * (h.lk_P[l] & 7);
-    }
+    int tx, ty;
+    lk_tile(h, l, tx, ty);
     for (int p = 0; p < h.n_pairs; ++p)
         if (h.lw[p][l] > 65535 || h.lh[p][l] > 65535 || c->need_h[p][l].size() != (size_t)h.lw[p][l] * h.lh[p][l]) {
             h.lk_tiles[l] = nullptr;   // set_lk_tiles' grid stays
@@ -577,7 +600,7 @@ vs_status vs_create(const vs_rig* rig, const vs_params* prm, vs_ctx** out)
             const int p = f >> 1;
             n16 += ((h.lw[p][l] + LKW_TX - 1) / LKW_TX) * ((h.lh[p][l] + 15) / 16);
         }
-        set_lk_tiles(h, l, P.lk_radius == LK_R_MAX ? default_lk_P(n16, lk_resident_blocks()) : 0);
+        set_lk_tiles(h, l, P.lk_radius == LK_R_MAX ? default_lk_P(n16, lk_resident_blocks()) : 0, level_px(h, l));
     }
     // ---- workspace arena ----
     size_t off = 0;
@@ -713,7 +736,7 @@ vs_status vs_create(const vs_rig* rig, const vs_params* prm, vs_ctx** out)
         vs_tune_entry te;
         if (vs_tune_key_of(c, &k) == VS_OK && vs_tune_get(&k, &te) == VS_OK) {
             for (int l = 0; l < h.levels; ++l)
-                if (h.lk_P[l] > 0 && te.flow_variant[l] > 0) set_lk_tiles(h, l, te.flow_variant[l]);
+                if (h.lk_P[l] > 0 && te.flow_variant[l] > 0) set_lk_tiles(h, l, te.flow_variant[l], level_px(h, l));
             if (te.pyr_tile_rows && P.pyr_tile_rows == 0) set_pyr_rows(h, te.pyr_tile_rows);
         }
     }
@@ -968,9 +991,9 @@ vs_status vs_stitch(vs_ctx* c, const uint8_t* const frames[], const vs_color_sta
     return VS_OK;
 }
 
-vs_status vs_set_flow_variant(vs_ctx* c, int level, int variant)
+// px: the pixels of the level's launch
+static vs_status set_flow_variant(vs_ctx* c, int level, int variant, long px)
 {
-    if (!c || level < 0 || level >= c->hp.levels) return VS_E_INVAL;
     if (c->sticky) return VS_E_DEVICE;
     if (!(variant == 0 || ((variant & 7) >= 1 && (variant & 7) <= 4 && (variant & ~31) == 0))) return VS_E_INVAL;
     if (variant > 0 && c->hp.lk_radius != LK_R_MAX) return fail(c, VS_E_UNSUPPORTED, "9x9 kernel needs lk_radius 4");
@@ -979,11 +1002,17 @@ vs_status vs_set_flow_variant(vs_ctx* c, int level, int variant)
     }
     if (variant > 0 && c->hp.lk_qcap[level] == 0) return fail(c, VS_E_UNSUPPORTED, "no deferral queue for this level");
     VS_CHECK(hipDeviceSynchronize(), "hipDeviceSynchronize");
-    set_lk_tiles(c->hp, level, variant);
+    set_lk_tiles(c->hp, level, variant, px);
     VS_CHECK(band_tiles(c, level), "flow tiles");
     VS_CHECK(hipMemcpy(c->dp, &c->hp, sizeof(DevPlan), hipMemcpyHostToDevice), "hipMemcpy plan");
     c->gen += 1;
     return VS_OK;
+}
+
+vs_status vs_set_flow_variant(vs_ctx* c, int level, int variant)
+{
+    if (!c || level < 0 || level >= c->hp.levels) return VS_E_INVAL;
+    return set_flow_variant(c, level, variant, level_px(c->hp, level));
 }
 
 // ---------------------------------------------------------------------------
@@ -1285,8 +1314,10 @@ vs_status capture(vs_batch* b)
 
 vs_status set_variant_all(vs_batch* b, int level, int variant)
 {
+    long px = 0;
+    for (int c = 0; c < b->n; ++c) px += level_px(b->ctx[c]->hp, level);
     for (int c = 0; c < b->n; ++c) {
-        vs_status st = vs_set_flow_variant(b->ctx[c], level, variant);
+        vs_status st = set_flow_variant(b->ctx[c], level, variant, px);
         if (st != VS_OK) return st;
     }
     return VS_OK;
@@ -1554,7 +1585,7 @@ bool flow_plan(int w, int h, const vs_params& P, DevPlan& d, FlowLayout& L)
             d.pyr_off[l][fl + 1] = d.pyr_off[l][fl] + d.pyr_tx[l][fl] * ((d.lh[0][l] + PYR_TY - 1) / PYR_TY);
         }
         const int n16 = 2 * ((d.lw[0][l] + LKW_TX - 1) / LKW_TX) * ((d.lh[0][l] + 15) / 16);
-        set_lk_tiles(d, l, P.lk_radius == LK_R_MAX ? default_lk_P(n16, lk_resident_blocks()) : 0);
+        set_lk_tiles(d, l, P.lk_radius == LK_R_MAX ? default_lk_P(n16, lk_resident_blocks()) : 0, level_px(d, l));
     }
     size_t off = 0;
     for (int l = 0; l < d.levels; ++l) {

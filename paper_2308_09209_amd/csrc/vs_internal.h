@@ -26,6 +26,10 @@ constexpr int LK_R_MAX = 4;                   // window half-size limit of the s
 constexpr int LK_D = 8;                       // displacement the staged moving tile covers
 constexpr int LKW_TX = 64;                    // 9x9-window flow kernel: 64 px wide, 4 * P rows,
                                               // P vertically adjacent pixels per thread
+// forms of the flow kernel at 1 px per thread finishing in-block: the general one,
+// with the gradient window held in registers, with 4 lanes per pixel (16 x 4 px tiles)
+enum { LK_GENERAL = 0, LK_HELD = 1, LK_LANES4 = 4 };
+constexpr int LK_SPLIT_TX = 16;
 constexpr int BL_TX = 256, BL_TY = 8;         // blend / balance tile: 256 x 8 px
 constexpr int BL_THREADS = 256;               // 4 px per thread, 2 rows per thread
 constexpr int SURR_UP_PX = 4;                 // surrogate upsampling: pixels per thread (rows 4 apart)
@@ -96,7 +100,8 @@ struct DevPlan {
     int32_t pyrf_off[2 * MAXP + 1], pyrf_tx[2 * MAXP];             // fused levels 0-2: level-2 tiles
     int32_t pyrf_ty;                                               // their height: 16, or 8 for small strips
     int32_t lk_off[MAXL][2 * MAXP + 1], lk_tx[MAXL][2 * MAXP];     // field f = 2 p + dir
-    int32_t lk_P[MAXL];               // 0: generic kernel (16 x 16 tiles); 1, 2, 4: 9x9 kernel, P px per thread
+    int32_t lk_P[MAXL];               // 0: generic kernel (16 x 16 tiles); 1 - 4: 9x9 kernel, P px per thread
+    int32_t lk_form[MAXL];            // LK_GENERAL, or a small-level form
     // flow tiles of a level as a list: tile b (fields back to back, from
     // lk_off) has its origin at x0 = lk_tiles[l][b] & 0xffff, y0 = lk_tiles[l][b] >> 16;
     // null: the box grid, lk_tx tiles per row

@@ -265,6 +265,33 @@ def test_deferred_flow_pixels_match_oracle():
         st.close()
 
 
+@pytest.mark.parametrize("w,h,scale,lam,iters", [
+    (2, 2, 1.0, 256.0, 5), (17, 5, 1.0, 256.0, 5), (64, 117, 1.0, 1e-3, 6), (120, 125, 1.0, 256.0, 5),   # 4 lanes
+    (65, 33, 1e-22, 256.0, 5), (65, 33, 1e12, 1e-12, 5), (97, 61, 1.0, 256.0, 1),      # the plain division
+    (121, 125, 1.0, 1e-3, 5), (250, 150, 1.0, 256.0, 5),                               # gradients held
+    (251, 150, 1.0, 1e-3, 5), (600, 260, 1e-22, 256.0, 4), (601, 700, 1.0, 1e-3, 5)])  # general, 1 to 4 px per thread
+def test_flow_forms_by_level_size_match_oracle(w, h, scale, lam, iters):
+    """Level sizes on both sides of each form of the flow kernel, weak
+    regularisation (displacements that leave the staged tile) and luma scales
+    whose quotients the shortened division does not take: both flows bit for bit
+    against the oracle."""
+    rng = np.random.default_rng(w * 1000 + h)
+    T = np.clip(np.cumsum(rng.normal(size=(h, w)), axis=1) * 12 + 128, 0, 255).round().astype(np.float32)
+    M = np.clip(np.roll(T, (1, 2), axis=(0, 1)) + rng.normal(size=T.shape) * 3, 0, 255).round().astype(np.float32)
+    T, M = (T * np.float32(scale)).astype(np.float32), (M * np.float32(scale)).astype(np.float32)
+
+    def pyr(a):
+        out = [a]
+        for _ in range(3):
+            out.append(O.pyr_down(out[-1]))
+        return out
+    say(f"[flow {w}x{h}] scale {scale} lambda {lam} steps {iters}")
+    a, b = V.PlainFlow(w, h, lk_lambda=lam, lk_iters=iters)(torch.from_numpy(T).cuda(), torch.from_numpy(M).cuda())
+    lf = np.float32(lam)
+    np.testing.assert_array_equal(a.cpu().numpy(), O.pyramid_flow(pyr(T), pyr(M), iters=iters, lam=lf))
+    np.testing.assert_array_equal(b.cpu().numpy(), O.pyramid_flow(pyr(M), pyr(T), iters=iters, lam=lf))
+
+
 @pytest.mark.parametrize("rows", [8, 16])
 def test_fused_pyramid_tile_heights(rows):
     """levels 0-2 in one pass at either level-2 tile height: every pyramid
