@@ -1,5 +1,5 @@
 // vs_device.h -- device helpers shared by the kernel sources of libvstitch
-// (vs_kernels.hip, vs_flow.hip) and the host-side group launch helper.
+// (vs_kernels.hip, vs_flow.hip, vs_var.hip) and the host-side group launch helper.
 #pragma once
 #include <algorithm>
 
@@ -125,6 +125,46 @@ __device__ __forceinline__ float capply(const float s[3], const float* __restric
 {
     float t = __builtin_fmaf(s[0], M[c], __builtin_fmaf(s[1], M[3 + c], s[2] * M[6 + c]));
     return clampf(t, 0.0f, 255.0f);
+}
+
+// Quotients, correctly rounded (the same bits as the division operator): the reciprocal y of d, itself correctly rounded, then for each
+// numerator q = n y and twice the remainder step q + (n - q d) y, the second from a
+// quotient within one unit in the last place, which rounds correctly (Markstein,
+// "Computation of elementary functions on the IBM RISC System/6000", 1990).
+// No intermediate leaves the normal range for d in [DIV_LO, DIV_HI] and numerators
+// that are 0 or between 2^-60 and 2^60 in magnitude.  The remainder is formed
+// negated, so that zeros keep their sign.  20 plain multiplications and additions
+// where the two operators take 40 instructions, half of them at the half rate.
+constexpr float DIV_LO = 0x1p-40f, DIV_HI = 0x1p60f;
+
+__device__ __forceinline__ float div_rcp(float d)
+{
+    const float y = __builtin_amdgcn_rcpf(d);
+    return __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
+}
+
+__device__ __forceinline__ bool div_ok(float n0, float n1)
+{
+    const float a = fabsf(n0), b = fabsf(n1);
+    return fmaxf(a, b) <= 0x1p60f && (a >= 0x1p-60f || a == 0.0f) && (b >= 0x1p-60f || b == 0.0f);
+}
+
+__device__ __forceinline__ float div_by(float n, float d, float y)
+{
+    float q = n * y;
+    q = __builtin_fmaf(-__builtin_fmaf(d, q, -n), y, q);
+    return __builtin_fmaf(-__builtin_fmaf(d, q, -n), y, q);
+}
+
+// 0.5 / sqrt(x), both correctly rounded, for x in [2^-100, 2^100]: the root from the
+// hardware's reciprocal root and one remainder step (every float of that range from
+// 2^-8 up checked against the operator), then its reciprocal as above.
+__device__ __forceinline__ float half_rsqrt(float x)
+{
+    const float y = __builtin_amdgcn_rsqf(x);
+    float s = x * y;
+    s = __builtin_fmaf(__builtin_fmaf(-s, s, x), 0.5f * y, s);
+    return 0.5f * div_rcp(s);
 }
 
 __device__ __forceinline__ int batch_block(const Batch& B, int b, int& c)

@@ -258,36 +258,6 @@ __device__ __forceinline__ void lk_finish(const DevPlan* __restrict__ Pl, int l,
     }
 }
 
-// Two quotients by one divisor, correctly rounded (the same bits as the division
-// operator): the reciprocal y of d, itself correctly rounded, then for each
-// numerator q = n y and twice the remainder step q + (n - q d) y, the second from a
-// quotient within one unit in the last place, which rounds correctly (Markstein,
-// "Computation of elementary functions on the IBM RISC System/6000", 1990).
-// No intermediate leaves the normal range for d in [DIV_LO, DIV_HI] and numerators
-// that are 0 or between 2^-60 and 2^60 in magnitude.  The remainder is formed
-// negated, so that zeros keep their sign.  20 plain multiplications and additions
-// where the two operators take 40 instructions, half of them at the half rate.
-constexpr float DIV_LO = 0x1p-40f, DIV_HI = 0x1p60f;
-
-__device__ __forceinline__ float div_rcp(float d)
-{
-    const float y = __builtin_amdgcn_rcpf(d);
-    return __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
-}
-
-__device__ __forceinline__ bool div_ok(float n0, float n1)
-{
-    const float a = fabsf(n0), b = fabsf(n1);
-    return fmaxf(a, b) <= 0x1p60f && (a >= 0x1p-60f || a == 0.0f) && (b >= 0x1p-60f || b == 0.0f);
-}
-
-__device__ __forceinline__ float div_by(float n, float d, float y)
-{
-    float q = n * y;
-    q = __builtin_fmaf(-__builtin_fmaf(d, q, -n), y, q);
-    return __builtin_fmaf(-__builtin_fmaf(d, q, -n), y, q);
-}
-
 // A Gauss-Newton step's rows as a list of units in order: tile row t, then pixel
 // q; pixel q interpolates its moving-image row k = t - q along x and uses it at
 // once with gradient row t (window row k, sums SA) and t - 1 (window row k - 1,

@@ -41,7 +41,11 @@ static_assert(STRIP_TY % SURR_UP_ROWS == 0, "whole upsampling blocks per strip t
 // Sums that many blocks add to are kept in several copies (tile t adds to copy
 // t % SPREAD, the consumer adds the copies): device-scope atomics on one
 // address from every block of a large grid serialise in the memory system.
-constexpr int VAR_TX = 64, VAR_TY = 8;        // variational Jacobi tile: 256 threads, 2 px each
+// variational Jacobi: VAR_T steps per launch on a region of 64 columns x 8 or 16 rows
+// (VAR_WV wavefronts, 1 or 2 px per thread; var_rows of the plan), of which VAR_OX x var_oy(rows) pixels are written
+constexpr int VAR_T = 2, VAR_TX = 64, VAR_WV = 8;
+constexpr int VAR_OX = VAR_TX - 3 * (VAR_T - 1);
+constexpr int var_oy(int rows) { return rows - 3 * (VAR_T - 1); }
 constexpr int HIST_SPREAD = 16, MOM_SPREAD = 32, PANO_SPREAD = 32, CSUM_SPREAD = 4;
 constexpr int SOLVE_THREADS = 256;
 enum { MOM_A = 0, MOM_N = 6, MOM_B = 7 };   // mom[][][]: A (6), n, B (9): 16 sums, one 128-byte line
@@ -85,7 +89,8 @@ struct DevPlan {
     float var_alpha, var_gamma;
     int32_t var_outer, var_inner;
     int32_t var_off[MAXL][2 * MAXP + 1];
-    int32_t var_toff[MAXL][2 * MAXP + 1];   // flow = 2: Jacobi tiles (VAR_TX x VAR_TY) per field, prefix sums
+    int32_t var_toff[MAXL][2 * MAXP + 1];   // flow = 2: Jacobi tiles (VAR_OX x var_oy) per field, prefix sums
+    int32_t var_rows[MAXL];                 // their region's rows
     float lk_lambda;
     double ridge;
     int32_t cam_w[MAXC], cam_h[MAXC], cam_pitch[MAXC];

@@ -92,7 +92,40 @@ __global__ __launch_bounds__(256) void k_var_deriv(const Batch B, int l)
 }
 
 // Level start: the flow is 0 at the coarsest level, else 2 x the bilinear
-// sample of the coarser level's flow at (x / 2 - 1/4, y / 2 - 1/4).
+// sample of the coarser level's flow at (x / 2 - 1/4, y / 2 - 1/4).  `added`: the
+// coarser level's last increments have not been folded into its flow; each sampled
+// flow takes them.
+__device__ __forceinline__ float2 var_start(const DevPlan* __restrict__ P, int p, int dir, int l, int x, int y, bool added)
+{
+    if (l + 1 >= P->levels) return make_float2(0.0f, 0.0f);
+    const int wc = P->lw[p][l + 1], hc = P->lh[p][l + 1];
+    const float2* __restrict__ uc = P->flow[p][dir][l + 1];
+    const float2* __restrict__ dc = P->var_dd[p][dir][l + 1][0];
+    const float cx = clampf(__builtin_fmaf((float)x, 0.5f, -0.25f), 0.0f, (float)(wc - 1));
+    const float cy = clampf(__builtin_fmaf((float)y, 0.5f, -0.25f), 0.0f, (float)(hc - 1));
+    const float flx = floorf(cx), fly = floorf(cy);
+    const int xa = (int)flx, ya = (int)fly;
+    const float fx = cx - flx, fy = cy - fly;
+    const int xb = xa + 1 < wc ? xa + 1 : wc - 1, yb = ya + 1 < hc ? ya + 1 : hc - 1;
+    const size_t q[4] = {(size_t)ya * wc + xa, (size_t)ya * wc + xb, (size_t)yb * wc + xa, (size_t)yb * wc + xb};
+    float2 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[i] = uc[q[i]];
+        if (added) {
+            const float2 d = dc[q[i]];
+            v[i] = make_float2(v[i].x + d.x, v[i].y + d.y);
+        }
+    }
+    float a = __builtin_fmaf(fx, v[1].x - v[0].x, v[0].x);
+    float b = __builtin_fmaf(fx, v[3].x - v[2].x, v[2].x);
+    const float ux = 2.0f * __builtin_fmaf(fy, b - a, a);
+    a = __builtin_fmaf(fx, v[1].y - v[0].y, v[0].y);
+    b = __builtin_fmaf(fx, v[3].y - v[2].y, v[2].y);
+    return make_float2(ux, 2.0f * __builtin_fmaf(fy, b - a, a));
+}
+
+// The level start by itself (without warps the level ends there).
 __global__ __launch_bounds__(256) void k_var_init(const Batch B, int l)
 {
     int c;
@@ -102,33 +135,16 @@ __global__ __launch_bounds__(256) void k_var_init(const Batch B, int l)
     if (!var_pixel(P, l, b, f, x, y, w, h)) return;
     const int p = f >> 1, dir = f & 1;
     if (kept_by_surrogate(P, p)) return;
-    float ux = 0.0f, uy = 0.0f;
-    if (l + 1 < P->levels) {
-        const int wc = P->lw[p][l + 1], hc = P->lh[p][l + 1];
-        const float2* __restrict__ uc = P->flow[p][dir][l + 1];
-        const float cx = clampf(__builtin_fmaf((float)x, 0.5f, -0.25f), 0.0f, (float)(wc - 1));
-        const float cy = clampf(__builtin_fmaf((float)y, 0.5f, -0.25f), 0.0f, (float)(hc - 1));
-        const float flx = floorf(cx), fly = floorf(cy);
-        const int xa = (int)flx, ya = (int)fly;
-        const float fx = cx - flx, fy = cy - fly;
-        const int xb = xa + 1 < wc ? xa + 1 : wc - 1, yb = ya + 1 < hc ? ya + 1 : hc - 1;
-        const float2 p00 = uc[(size_t)ya * wc + xa], p10 = uc[(size_t)ya * wc + xb];
-        const float2 p01 = uc[(size_t)yb * wc + xa], p11 = uc[(size_t)yb * wc + xb];
-        float a = __builtin_fmaf(fx, p10.x - p00.x, p00.x);
-        float bb = __builtin_fmaf(fx, p11.x - p01.x, p01.x);
-        ux = 2.0f * __builtin_fmaf(fy, bb - a, a);
-        a = __builtin_fmaf(fx, p10.y - p00.y, p00.y);
-        bb = __builtin_fmaf(fx, p11.y - p01.y, p01.y);
-        uy = 2.0f * __builtin_fmaf(fy, bb - a, a);
-    }
-    P->flow[p][dir][l][(size_t)y * w + x] = make_float2(ux, uy);
+    P->flow[p][dir][l][(size_t)y * w + x] = var_start(P, p, dir, l, x, y, false);
 }
 
 // One warp: the moving image and its derivatives sampled at x + (u, v), the
-// data and gradient terms' coefficients (Iz Ix Iy Ixz Iyz Ixx Ixy Iyy), and
-// the increments reset.  With `fold` the previous warp's increments are first
-// added to the flow.
-__global__ __launch_bounds__(256) void k_var_warp(const Batch B, int l, int fold)
+// data and gradient terms' coefficients (Iz Ix Iy Ixz Iyz Ixx Ixy Iyy).  The flow is
+// the level's start at the first warp (a pass of its own before it took 20 us at
+// level 0 of the 4 x 1080p ring), later the previous warp's with its increments
+// added.  `reset`: the increments are set to 0 (no Jacobi steps follow: the first of
+// those takes 0 by itself).
+__global__ __launch_bounds__(256) void k_var_warp(const Batch B, int l, int first, int reset)
 {
     int c;
     const int b = batch_block(B, blockIdx.x, c);
@@ -141,12 +157,15 @@ __global__ __launch_bounds__(256) void k_var_warp(const Batch B, int l, int fold
     const size_t n = (size_t)w * h, q = (size_t)y * w + x;
     float2* __restrict__ U = P->flow[p][dir][l];
     float2* __restrict__ dd = P->var_dd[p][dir][l][0];
-    float2 u = U[q];
-    if (fold) {
+    float2 u;
+    if (first) {
+        u = var_start(P, p, dir, l, x, y, true);
+    } else {
+        u = U[q];
         const float2 d = dd[q];
         u = make_float2(u.x + d.x, u.y + d.y);
-        U[q] = u;
     }
+    U[q] = u;
     const float X = (float)x + u.x, Y = (float)y + u.y;
     const float* __restrict__ Mv = P->pyr[p][mc][l];
     const float* __restrict__ MD = P->var_D[p][mc][l];
@@ -163,22 +182,123 @@ __global__ __launch_bounds__(256) void k_var_warp(const Batch B, int l, int fold
     co[5 * n + q] = mxx;
     co[6 * n + q] = mxy;
     co[7 * n + q] = myy;
-    dd[q] = make_float2(0.0f, 0.0f);
+    if (reset) dd[q] = make_float2(0.0f, 0.0f);
 }
 
-// One Jacobi step of the linearised equations, increments src -> dst, on a
-// VAR_TX x VAR_TY tile of one field.  The sums V = U + dU of the tile and a
-// ring (one pixel left and up, two right and down) go to LDS once; from them
-// the smoothness Psi' of the tile and a one-pixel ring (forward differences of
-// V, 0 beyond the last column / row of the level), then each pixel's update
-// from its 4 neighbours in the level.  Same operations as the per-pixel form:
-// every V is the same sum, every Psi' the same expression.
-__global__ __launch_bounds__(256) void k_var_jacobi(const Batch B, int l, int src)
+// VAR_T Jacobi steps of the linearised equations in one launch, increments src ->
+// src ^ 1 (first: the increments before them are 0 and not read).  A block of 8
+// wavefronts holds a region of 64 columns x 8 NP rows of one field, NP pixels per
+// thread; a pixel's step reads one pixel to the left and up and two to the right and
+// down, so each step makes good one column and row less at the start and two less at
+// the end, and the block writes the pixels that are right after the last.  Per step
+// the sums V = U + dU of the region and its ring (the ring as loaded: what it makes
+// wrong is not written) lie in LDS; from them the smoothness Psi' of the region and
+// a one-pixel ring (forward differences of V, 0 beyond the last column / row of the
+// level), then each pixel's update from its 4 neighbours in the level.  Same
+// operations as the per-pixel form: every V is the same sum, every Psi' the same
+// expression.  The coefficients and the flow stay in registers over the steps.
+// Bound by memory at the large levels (49 B read and 8 B written per pixel and
+// launch; one step per launch moved them at the rate of a copy) and by the steps'
+// latency at the small ones.  4 x 1080p ring, per step, levels 0 to 3: one step per
+// launch 50.5, 20.4, 8.9, 7.2 us; this form 29, 12, 5.5, 3.7 us (with 32-row regions, 4 pixels
+// per thread, 40 us at level 0: fewer wavefronts; with 1024 threads 30 us).
+
+// 0.5 / sqrt(x) of the Charbonnier terms: x >= VAR_EPS2, or not a number
+__device__ __forceinline__ float var_weight(float x)
 {
-    constexpr int RW = VAR_TX + 3, RH = VAR_TY + 3;   // V region: x0-1 .. x0+TX+1
-    constexpr int SW = VAR_TX + 2, SH = VAR_TY + 2;   // Psi' region: x0-1 .. x0+TX
+    return __any(x > 0x1p100f) ? 0.5f / sqrtf(x) : half_rsqrt(x);
+}
+
+// Psi' of smoothness at a position with the sums v0, r to its right and d below
+__device__ __forceinline__ float var_psi(float2 v0, float2 r, float2 d, bool right, bool down)
+{
+    const float ux = right ? r.x - v0.x : 0.0f, vx = right ? r.y - v0.y : 0.0f;
+    const float uy = down ? d.x - v0.x : 0.0f, vy = down ? d.y - v0.y : 0.0f;
+    return var_weight(__builtin_fmaf(ux, ux, __builtin_fmaf(uy, uy, __builtin_fmaf(vx, vx, __builtin_fmaf(vy, vy, VAR_EPS2)))));
+}
+
+// EDGE: the region or its ring leaves the level
+template <int NP, bool EDGE>
+__device__ __forceinline__ void var_steps(const int w, const int h, const int x0, const int y0, const float alpha,
+                                          const float gamma, const float (&cf)[NP][8], const float2 (&u)[NP],
+                                          float2 (&dq)[NP], uint32_t nd, float2* sV, float* sS)
+{
+    constexpr int ROWS = VAR_WV * NP, RW = VAR_TX + 3, SW = VAR_TX + 2;
+    const int tid = threadIdx.x, lx = tid & 63, wv = tid >> 6;
+    // this thread's position of Psi's ring: rows -1 and ROWS, columns -1 and 64
+    constexpr int NRING = 2 * SW + 2 * ROWS;
+    static_assert(NRING <= 64 * VAR_WV, "a ring position per thread");
+    const int rr = tid < 2 * SW ? (tid < SW ? -1 : ROWS) : (tid - 2 * SW) >> 1;
+    const int rc = tid < 2 * SW ? (tid < SW ? tid : tid - SW) - 1 : ((tid - 2 * SW) & 1 ? VAR_TX : -1);
+    for (int t = 0; t < VAR_T; ++t) {
+        if (t > 0) __syncthreads();   // every pixel has read its neighbours
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int ty = wv + VAR_WV * k;
+            float2 v = make_float2(u[k].x + dq[k].x, u[k].y + dq[k].y);
+            if (EDGE && !(x0 + lx >= 0 && x0 + lx < w && y0 + ty >= 0 && y0 + ty < h)) v = make_float2(0.0f, 0.0f);
+            sV[(1 + ty) * RW + 1 + lx] = v;
+        }
+        __syncthreads();
+        auto psi = [&](int r, int c) {   // at region row r, column c
+            const int vi = (r + 1) * RW + c + 1, xx = x0 + c, yy = y0 + r;
+            const float s = var_psi(sV[vi], sV[vi + 1], sV[vi + RW], !EDGE || xx + 1 < w, !EDGE || yy + 1 < h);
+            sS[(r + 1) * SW + c + 1] = EDGE && (xx < 0 || xx >= w || yy < 0 || yy >= h) ? 0.0f : s;
+        };
+#pragma unroll 1
+        for (int k = 0; k < NP; ++k) psi(wv + VAR_WV * k, lx);
+        if (tid < NRING) psi(rr, rc);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int ty = wv + VAR_WV * k, x = x0 + lx, y = y0 + ty;
+            float A11 = 0.0f, A12 = 0.0f, A22 = 0.0f, b1 = 0.0f, b2 = 0.0f;
+            if (nd >> k & 1u) {
+                const float c0 = cf[k][0], c1 = cf[k][1], c2 = cf[k][2], c3 = cf[k][3];
+                const float c4 = cf[k][4], c5 = cf[k][5], c6 = cf[k][6], c7 = cf[k][7];
+                const float e = __builtin_fmaf(c2, dq[k].y, __builtin_fmaf(c1, dq[k].x, c0));
+                const float pd = var_weight(__builtin_fmaf(e, e, VAR_EPS2));
+                const float gx = __builtin_fmaf(c6, dq[k].y, __builtin_fmaf(c5, dq[k].x, c3));
+                const float gy = __builtin_fmaf(c7, dq[k].y, __builtin_fmaf(c6, dq[k].x, c4));
+                const float pg = gamma * var_weight(__builtin_fmaf(gx, gx, __builtin_fmaf(gy, gy, VAR_EPS2)));
+                A11 = __builtin_fmaf(pd, c1 * c1, pg * __builtin_fmaf(c5, c5, c6 * c6));
+                A12 = __builtin_fmaf(pd, c1 * c2, pg * __builtin_fmaf(c5, c6, c6 * c7));
+                A22 = __builtin_fmaf(pd, c2 * c2, pg * __builtin_fmaf(c6, c6, c7 * c7));
+                b1 = -__builtin_fmaf(pd, c1 * c0, pg * __builtin_fmaf(c5, c3, c6 * c4));
+                b2 = -__builtin_fmaf(pd, c2 * c0, pg * __builtin_fmaf(c6, c3, c7 * c4));
+            }
+            const int si = (ty + 1) * SW + lx + 1, vi = (ty + 1) * RW + lx + 1;
+            const float s0 = sS[si];
+            float S = 0.0f, Su = 0.0f, Sv = 0.0f;
+            const bool has[4] = {x >= 1, x + 1 < w, y >= 1, y + 1 < h};
+            const int so[4] = {-1, 1, -SW, SW}, vo[4] = {-1, 1, -RW, RW};
+#pragma unroll
+            for (int n = 0; n < 4; ++n) {
+                const float wn = 0.5f * (s0 + sS[si + so[n]]);
+                const float2 vn = sV[vi + vo[n]];
+                if (!EDGE || has[n]) {
+                    S += wn;
+                    Su = __builtin_fmaf(wn, vn.x - u[k].x, Su);
+                    Sv = __builtin_fmaf(wn, vn.y - u[k].y, Sv);
+                }
+            }
+            const float nx = __builtin_fmaf(alpha, Su, __builtin_fmaf(-A12, dq[k].y, b1)), dx = __builtin_fmaf(alpha, S, A11);
+            const float ny = __builtin_fmaf(alpha, Sv, __builtin_fmaf(-A12, dq[k].x, b2)), dy = __builtin_fmaf(alpha, S, A22);
+            const bool ok = fminf(dx, dy) >= DIV_LO && fmaxf(dx, dy) <= DIV_HI && div_ok(nx, ny);
+            if (__any(!ok))
+                dq[k] = make_float2(nx / dx, ny / dy);
+            else
+                dq[k] = make_float2(div_by(nx, dx, div_rcp(dx)), div_by(ny, dy, div_rcp(dy)));
+        }
+    }
+}
+
+template <int NP>
+__global__ __launch_bounds__(64 * VAR_WV) void k_var_jacobi(const Batch B, int l, int src, int first)
+{
+    constexpr int ROWS = VAR_WV * NP, RW = VAR_TX + 3, RH = ROWS + 3, SW = VAR_TX + 2;
     __shared__ float2 sV[RH * RW];
-    __shared__ float sS[SH * SW];
+    __shared__ float sS[(ROWS + 2) * SW];
     int c;
     const int b = batch_block(B, blockIdx.x, c);
     const DevPlan* __restrict__ P = B.plan[c];
@@ -186,105 +306,56 @@ __global__ __launch_bounds__(256) void k_var_jacobi(const Batch B, int l, int sr
     const int p = f >> 1, dir = f & 1;
     if (kept_by_surrogate(P, p)) return;
     const int w = P->lw[p][l], h = P->lh[p][l];
-    const int t = b - P->var_toff[l][f], ntx = (w + VAR_TX - 1) / VAR_TX;
-    const int x0 = (t % ntx) * VAR_TX, y0 = (t / ntx) * VAR_TY;
+    constexpr int lost = VAR_T - 1, OX = VAR_OX, OY = var_oy(ROWS);   // pixels written
+    const int t = b - P->var_toff[l][f], ntx = (w + OX - 1) / OX;
+    const int x0 = (t % ntx) * OX - lost, y0 = (t / ntx) * OY - lost;
     const float2* __restrict__ U = P->flow[p][dir][l];
     const float2* __restrict__ d = P->var_dd[p][dir][l][src];
-    const int tid = threadIdx.x;
+    const uint8_t* __restrict__ need = P->need[p][l];
+    const int tid = threadIdx.x, lx = tid & 63, wv = tid >> 6;
     const size_t n = (size_t)w * h;
     const float* __restrict__ co = P->var_co[p][dir][l];
-    const int x = x0 + (tid & 63);
-    // this thread's pixels' own values, loaded before the staging so that
-    // their latency overlaps it
-    constexpr int NP = VAR_TY / 4;
+    // this thread's pixels' values (outside the level: the nearest one's, unused)
     float cf[NP][8];
-    float2 uo[NP], dqo[NP];
-    bool in[NP], nd[NP];
+    float2 u[NP], dq[NP];
+    uint32_t nd = 0;
+    const int xc = clampi(x0 + lx, 0, w - 1);
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
-        const int y = y0 + (tid >> 6) + 4 * k;
-        in[k] = x < w && y < h;
-        const size_t q = in[k] ? (size_t)y * w + x : 0;
-        uo[k] = U[q];
-        dqo[k] = d[q];
-        nd[k] = in[k] && P->need[p][l][q] != 0;
+        const size_t q = (size_t)clampi(y0 + wv + VAR_WV * k, 0, h - 1) * w + xc;
+        u[k] = U[q];
+        dq[k] = first ? make_float2(0.0f, 0.0f) : d[q];
+        nd |= (uint32_t)(need[q] != 0) << k;
 #pragma unroll
         for (int j = 0; j < 8; ++j) cf[k][j] = co[j * n + q];
     }
-    for (int i = tid; i < RH * RW; i += 256) {
-        const int xx = x0 - 1 + i % RW, yy = y0 - 1 + i / RW;
+    // the ring of V: row -1, rows ROWS and ROWS + 1, columns -1, 64 and 65
+    constexpr int NRING = 3 * RW + 3 * ROWS;
+    static_assert(NRING <= 64 * VAR_WV, "a ring position per thread");
+    if (tid < NRING) {
+        const int e = tid - 3 * RW;
+        const int r = tid < 3 * RW ? (tid < RW ? -1 : tid < 2 * RW ? ROWS : ROWS + 1) : e / 3;
+        const int cc = tid < 3 * RW ? tid % RW - 1 : (e % 3 == 0 ? -1 : VAR_TX - 1 + e % 3);
+        const int xx = x0 + cc, yy = y0 + r;
         float2 v = make_float2(0.0f, 0.0f);
         if (xx >= 0 && xx < w && yy >= 0 && yy < h) {
             const size_t q = (size_t)yy * w + xx;
-            const float2 a = U[q], da = d[q];
+            const float2 a = U[q], da = first ? make_float2(0.0f, 0.0f) : d[q];
             v = make_float2(a.x + da.x, a.y + da.y);
         }
-        sV[i] = v;
+        sV[(r + 1) * RW + cc + 1] = v;
     }
-    __syncthreads();
-    for (int i = tid; i < SH * SW; i += 256) {
-        const int sx = i % SW, sy = i / SW;                 // region position (x0 - 1 + sx, y0 - 1 + sy)
-        const int xx = x0 - 1 + sx, yy = y0 - 1 + sy;
-        float s = 0.0f;
-        if (xx >= 0 && xx < w && yy >= 0 && yy < h) {
-            const float2 v0 = sV[sy * RW + sx];
-            float ux = 0.0f, uy = 0.0f, vx = 0.0f, vy = 0.0f;
-            if (xx + 1 < w) {
-                const float2 r = sV[sy * RW + sx + 1];
-                ux = r.x - v0.x;
-                vx = r.y - v0.y;
-            }
-            if (yy + 1 < h) {
-                const float2 r = sV[(sy + 1) * RW + sx];
-                uy = r.x - v0.x;
-                vy = r.y - v0.y;
-            }
-            s = 0.5f / sqrtf(__builtin_fmaf(ux, ux, __builtin_fmaf(uy, uy, __builtin_fmaf(vx, vx,
-                                                    __builtin_fmaf(vy, vy, VAR_EPS2)))));
-        }
-        sS[i] = s;
-    }
-    __syncthreads();
     const float alpha = P->var_alpha, gamma = P->var_gamma;
+    if (x0 >= 1 && y0 >= 1 && x0 + VAR_TX + 2 <= w && y0 + ROWS + 2 <= h)
+        var_steps<NP, false>(w, h, x0, y0, alpha, gamma, cf, u, dq, nd, sV, sS);
+    else
+        var_steps<NP, true>(w, h, x0, y0, alpha, gamma, cf, u, dq, nd, sV, sS);
+    float2* __restrict__ out = P->var_dd[p][dir][l][src ^ 1];
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
-        const int ty = (tid >> 6) + 4 * k, y = y0 + ty;
-        if (!in[k]) continue;
-        const size_t q = (size_t)y * w + x;
-        const float2 u = uo[k], dq = dqo[k];
-        float A11 = 0.0f, A12 = 0.0f, A22 = 0.0f, b1 = 0.0f, b2 = 0.0f;
-        if (nd[k]) {
-            const float c0 = cf[k][0], c1 = cf[k][1], c2 = cf[k][2], c3 = cf[k][3];
-            const float c4 = cf[k][4], c5 = cf[k][5], c6 = cf[k][6], c7 = cf[k][7];
-            const float e = __builtin_fmaf(c2, dq.y, __builtin_fmaf(c1, dq.x, c0));
-            const float pd = 0.5f / sqrtf(__builtin_fmaf(e, e, VAR_EPS2));
-            const float gx = __builtin_fmaf(c6, dq.y, __builtin_fmaf(c5, dq.x, c3));
-            const float gy = __builtin_fmaf(c7, dq.y, __builtin_fmaf(c6, dq.x, c4));
-            const float pg = gamma * (0.5f / sqrtf(__builtin_fmaf(gx, gx, __builtin_fmaf(gy, gy, VAR_EPS2))));
-            A11 = __builtin_fmaf(pd, c1 * c1, pg * __builtin_fmaf(c5, c5, c6 * c6));
-            A12 = __builtin_fmaf(pd, c1 * c2, pg * __builtin_fmaf(c5, c6, c6 * c7));
-            A22 = __builtin_fmaf(pd, c2 * c2, pg * __builtin_fmaf(c6, c6, c7 * c7));
-            b1 = -__builtin_fmaf(pd, c1 * c0, pg * __builtin_fmaf(c5, c3, c6 * c4));
-            b2 = -__builtin_fmaf(pd, c2 * c0, pg * __builtin_fmaf(c6, c3, c7 * c4));
-        }
-        const int sx = (tid & 63) + 1, sy = ty + 1;          // (x, y) in the Psi' region
-        const float s0 = sS[sy * SW + sx];
-        float S = 0.0f, Su = 0.0f, Sv = 0.0f;
-        const int nx[4] = {x - 1, x + 1, x, x};
-        const int ny[4] = {y, y, y - 1, y + 1};
-        const int ox[4] = {-1, 1, 0, 0}, oy[4] = {0, 0, -1, 1};
-#pragma unroll
-        for (int k2 = 0; k2 < 4; ++k2) {
-            if (nx[k2] < 0 || nx[k2] >= w || ny[k2] < 0 || ny[k2] >= h) continue;
-            const float wn = 0.5f * (s0 + sS[(sy + oy[k2]) * SW + sx + ox[k2]]);
-            const float2 vn = sV[(sy + oy[k2]) * RW + sx + ox[k2]];
-            S += wn;
-            Su = __builtin_fmaf(wn, vn.x - u.x, Su);
-            Sv = __builtin_fmaf(wn, vn.y - u.y, Sv);
-        }
-        const float dx = __builtin_fmaf(alpha, Su, __builtin_fmaf(-A12, dq.y, b1)) / __builtin_fmaf(alpha, S, A11);
-        const float dy = __builtin_fmaf(alpha, Sv, __builtin_fmaf(-A12, dq.x, b2)) / __builtin_fmaf(alpha, S, A22);
-        P->var_dd[p][dir][l][src ^ 1][q] = make_float2(dx, dy);
+        const int ty = wv + VAR_WV * k, x = x0 + lx, y = y0 + ty;
+        if (lx >= lost && lx < lost + OX && ty >= lost && ty < lost + OY && x < w && y < h)
+            out[(size_t)y * w + x] = dq[k];
     }
 }
 
@@ -321,19 +392,29 @@ hipError_t launch_var(const Group& g, int l, hipStream_t s)
     int outer = g.hp[0]->var_outer, inner = g.hp[0]->var_inner;
     for (int c = 1; c < g.n; ++c)
         if (g.hp[c]->var_outer != outer || g.hp[c]->var_inner != inner) return hipErrorInvalidValue;
-    if (inner % 2) return hipErrorInvalidValue;   // the steps end in buffer 0
+    if (inner % VAR_T) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_var_deriv, grid, blk, 0, s, B, l);
-    hipLaunchKernelGGL(k_var_init, grid, blk, 0, s, B, l);
-    Batch BT;
-    make_batch(g, BT, [&](const DevPlan& h) {
-        return h.use_flow == 2 && h.flow_mode != VS_FLOW_SURROGATE && l < h.levels ? h.var_toff[l][2 * h.n_pairs] : 0;
-    });
-    const dim3 tgrid(BT.off[BT.n]);
+    if (outer == 0) hipLaunchKernelGGL(k_var_init, grid, blk, 0, s, B, l);
+    auto jacobi = [&](int src, int first) {
+        for (int rows = 8; rows <= 16; rows *= 2) {
+            Batch BT;
+            if (!make_batch(g, BT, [&](const DevPlan& h) {
+                    return h.use_flow == 2 && h.flow_mode != VS_FLOW_SURROGATE && l < h.levels && h.var_rows[l] == rows
+                               ? h.var_toff[l][2 * h.n_pairs] : 0; }))
+                continue;
+            const dim3 tg(BT.off[BT.n]);
+            if (rows == 8) hipLaunchKernelGGL(k_var_jacobi<1>, tg, dim3(512), 0, s, BT, l, src, first);
+            else hipLaunchKernelGGL(k_var_jacobi<2>, tg, dim3(512), 0, s, BT, l, src, first);
+        }
+    };
+    const int launches = inner / VAR_T;
     for (int o = 0; o < outer; ++o) {
-        hipLaunchKernelGGL(k_var_warp, grid, blk, 0, s, B, l, o > 0 ? 1 : 0);
-        for (int it = 0; it < inner; ++it) hipLaunchKernelGGL(k_var_jacobi, tgrid, blk, 0, s, BT, l, it & 1);
+        hipLaunchKernelGGL(k_var_warp, grid, blk, 0, s, B, l, o == 0 ? 1 : 0, launches == 0 ? 1 : 0);
+        // the last launch writes increment buffer 0
+        for (int it = 0; it < launches; ++it) jacobi((launches - it) & 1, it == 0 ? 1 : 0);
     }
-    if (outer > 0) hipLaunchKernelGGL(k_var_fold, grid, blk, 0, s, B, l);
+    // (a coarser level's last increments are added where the finer one starts)
+    if (outer > 0 && l == 0) hipLaunchKernelGGL(k_var_fold, grid, blk, 0, s, B, l);
     return hipGetLastError();
 }
 

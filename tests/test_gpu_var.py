@@ -62,6 +62,24 @@ def test_plain_flow_context_matches_oracle(kw):
     pf.close()
 
 
+@pytest.mark.parametrize("w,h,outer,inner,scale", [
+    (2, 2, 3, 10, 1.0), (61, 13, 3, 10, 1.0), (62, 14, 2, 4, 1.0), (123, 5, 3, 2, 1.0), (64, 6, 2, 0, 1.0),
+    (70, 40, 0, 10, 1.0), (130, 70, 1, 10, 1e16), (1300, 400, 2, 6, 1.0)])
+def test_jacobi_regions_and_step_counts_match_oracle(w, h, outer, inner, scale):
+    """levels on both sides of a region's width and height, both region heights, step
+    and warp counts down to 0 and a luma scale whose roots and quotients the
+    shortened forms do not take: every flow bit for bit against the oracle"""
+    T, M = _pair(h=h, w=w, seed=w + h)
+    T, M = (T * np.float32(scale)).astype(np.float32), (M * np.float32(scale)).astype(np.float32)
+    say(f"[var {w}x{h}] {outer} warps of {inner} steps, scale {scale}")
+    pf = V.PlainFlow(w, h, flow=2, var_outer=outer, var_inner=inner)
+    a, b = pf(cu(T), cu(M))
+    kw = dict(levels=V.default_params().lk_levels, outer=outer, inner=inner)
+    np.testing.assert_array_equal(a.cpu().numpy(), O.var_pyramid(T, M, **kw))
+    np.testing.assert_array_equal(b.cpu().numpy(), O.var_pyramid(M, T, **kw))
+    pf.close()
+
+
 @pytest.mark.parametrize("seed,ring,n", [(96, True, 3), (41, False, 3)])
 def test_stitch_with_variational_flow_matches_oracle(seed, ring, n):
     sc = small_scene(n_cams=n, W=200, H=110, overlap=0.35, ring=ring, seed_config=seed, drift=0.03)
