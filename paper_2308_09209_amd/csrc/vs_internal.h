@@ -31,7 +31,8 @@ constexpr int LKW_TX = 64;                    // 9x9-window flow kernel: 64 px w
 enum { LK_GENERAL = 0, LK_HELD = 1, LK_LANES4 = 4 };
 constexpr int LK_SPLIT_TX = 16;
 constexpr int BL_TX = 256, BL_TY = 8;         // blend / balance tile: 256 x 8 px
-constexpr int BL_THREADS = 256;               // 4 px per thread, 2 rows per thread
+constexpr int BL_THREADS = 256;               // balance: 4 px per thread, 2 rows per thread
+constexpr int BLEND_THREADS = 512;            // blend: 4 px per thread, 1 row
 constexpr int SURR_UP_PX = 4;                 // surrogate upsampling: pixels per thread (rows 4 apart)
 constexpr int SURR_UP_ROWS = 4 * SURR_UP_PX;  // 64 x 16 px per block
 constexpr int SURR_UP_SUB = STRIP_TY / SURR_UP_ROWS;   // upsampling blocks per strip tile

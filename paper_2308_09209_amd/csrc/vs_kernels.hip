@@ -231,17 +231,22 @@ __device__ __forceinline__ void strips_body(const DevPlan* __restrict__ P, const
     uint32_t* __restrict__ strip = P->strip[p];
     uint8_t* __restrict__ mask = P->mask[p];
     const int lx = tx0 + (tid & 63);
+    const float wj = (float)(P->cam_w[kj] - 1), hmj = (float)(P->cam_h[kj] - 1);
+    const float wi = (float)(P->cam_w[ki] - 1), hmi = (float)(P->cam_h[ki] - 1);
     uint32_t a00 = 0, a01 = 0, a02 = 0, a11 = 0, a12 = 0, a22 = 0, cnt = 0;
     for (int r = tid >> 6; r < STRIP_TY; r += 4) {
         const int ly = ty0 + r;
         if (lx >= sw || ly >= sh) continue;
         const int X = P->sx0[p] + lx, Y = P->sy0[p] + ly;
-        float u, v, rgb[3];
-        bool okj = hom(P->hinv[kj], (float)X, (float)Y, P->cam_w[kj], P->cam_h[kj], u, v);
-        bilin3(P->frame[kj], P->cam_pitch[kj], P->cam_w[kj], P->cam_h[kj], u, v, rgb);
+        float uj, vj, ui, vi, rgb[3];
+        BilTaps tj, ti;
+        const bool okj = hom(P->hinv[kj], (float)X, (float)Y, P->cam_w[kj], P->cam_h[kj], uj, vj);
+        bil_load(P->frame[kj], P->cam_pitch[kj], P->cam_h[kj], wj, wj - 1.0f, hmj, uj, vj, tj);
+        const bool oki = hom(P->hinv[ki], (float)(X - shift_i), (float)Y, P->cam_w[ki], P->cam_h[ki], ui, vi);
+        bil_load(P->frame[ki], P->cam_pitch[ki], P->cam_h[ki], wi, wi - 1.0f, hmi, ui, vi, ti);
+        bil_rgb(tj, rgb);
         uint32_t cj0 = round8(rgb[0]), cj1 = round8(rgb[1]), cj2 = round8(rgb[2]);
-        bool oki = hom(P->hinv[ki], (float)(X - shift_i), (float)Y, P->cam_w[ki], P->cam_h[ki], u, v);
-        bilin3(P->frame[ki], P->cam_pitch[ki], P->cam_w[ki], P->cam_h[ki], u, v, rgb);
+        bil_rgb(ti, rgb);
         uint32_t ci0 = round8(rgb[0]), ci1 = round8(rgb[1]), ci2 = round8(rgb[2]);
         const size_t q = (size_t)ly * sw + lx;
         strip[q] = cj0 | (cj1 << 8) | (cj2 << 16);
@@ -790,18 +795,48 @@ __global__ __launch_bounds__(256) void k_pyr_fused(const Batch B, int after)
 // neighbouring pixels often share a value, and same-address LDS atomics from
 // one instruction serialise (+ 1: a bin's copies in different banks)
 //
+// Bound by the VALU (25 M wavefront instructions per 4 x 1080p frame, most at 4
+// cycles) and its chains' latency at 5 wavefronts per SIMD.  4 x 1080p ring 73 -> 61
+// us, 8 x 4K 503 -> 436 us, with quotients by one reciprocal (hom_div), a path for
+// wavefronts inside one camera and one row per thread (512 threads) instead of two;
+// a like path for wavefronts inside one overlap needs 121 VGPRs: 79 and 575 us.
 // A thread's 4 pixels of a row: their 4 codes read at once, then per group of
 // BG pixels three phases, so that the memory reads of a group are in flight
 // together: (1) the covering candidates and their positions; the flows of the
 // two-camera pixels; (2) the bilinear taps of every sample (one camera: at its
 // position; two cameras: at the positions their flows move them to); (3)
 // colour correction, fusion, histogram.
+// one camera's constants from its LDS vectors (s_cam of blend_body)
+__device__ __forceinline__ void blend_camera(const uint32_t* c, float (&h)[9], float (&M)[9], float& wm1, float& hm1,
+                                             int& pitch, int& H, const uint8_t*& F)
+{
+    uint4 v[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) v[i] = reinterpret_cast<const uint4*>(c)[i];
+    const uint32_t w[24] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w, v[2].x, v[2].y, v[2].z, v[2].w,
+                            v[3].x, v[3].y, v[3].z, v[3].w, v[4].x, v[4].y, v[4].z, v[4].w, v[5].x, v[5].y, v[5].z, v[5].w};
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        h[i] = __uint_as_float(w[i]);
+        M[i] = __uint_as_float(w[12 + i]);
+    }
+    wm1 = __uint_as_float(w[9]);
+    hm1 = __uint_as_float(w[10]);
+    pitch = (int)w[11];
+    H = (int)w[21];
+    F = (const uint8_t*)((uintptr_t)w[22] | (uintptr_t)w[23] << 32);
+}
+
 __device__ __forceinline__ void blend_body(const DevPlan* __restrict__ P, const int bid,
                                            uint32_t (*s_hist)[3 * 256 + 1])
 {
     // per-camera constants of the frame, indexed by each lane's own camera
     __shared__ float s_hinv[MAXC][9], s_M[MAXC][9];
     __shared__ int s_cw[MAXC], s_ch[MAXC], s_cp[MAXC];
+    __shared__ float s_wm1[MAXC], s_hm1[MAXC];   // width and height less 1
+    // the same of one camera as six 16-byte vectors: homography (9), W - 1, H - 1,
+    // pitch, colour matrix (9), H, frame pointer (2)
+    __shared__ __align__(16) uint32_t s_cam[MAXC][24];
     __shared__ const uint8_t* s_fr[MAXC];
     // per-pair constants: pair of two cameras, camera j, flow-domain origin and
     // width, the two level-0 flows
@@ -809,8 +844,8 @@ __device__ __forceinline__ void blend_body(const DevPlan* __restrict__ P, const 
     __shared__ int s_pj[MAXP], s_fx0[MAXP], s_fy0[MAXP], s_fw[MAXP];
     __shared__ const float2* s_fl[MAXP][2];
     const int tid = threadIdx.x;
-    for (int i = tid; i < 8 * (3 * 256 + 1); i += BL_THREADS) (&s_hist[0][0])[i] = 0;
-    for (int i = tid; i < P->n_cams * 9; i += BL_THREADS) {
+    for (int i = tid; i < 8 * (3 * 256 + 1); i += BLEND_THREADS) (&s_hist[0][0])[i] = 0;
+    for (int i = tid; i < P->n_cams * 9; i += BLEND_THREADS) {
         (&s_hinv[0][0])[i] = (&P->hinv[0][0])[i];
         (&s_M[0][0])[i] = (&P->res->Mk[0][0])[i];
     }
@@ -818,6 +853,18 @@ __device__ __forceinline__ void blend_body(const DevPlan* __restrict__ P, const 
         s_cw[tid] = P->cam_w[tid];
         s_ch[tid] = P->cam_h[tid];
         s_cp[tid] = P->cam_pitch[tid];
+        s_wm1[tid] = (float)(P->cam_w[tid] - 1);
+        s_hm1[tid] = (float)(P->cam_h[tid] - 1);
+        for (int i = 0; i < 9; ++i) {
+            s_cam[tid][i] = __float_as_uint(P->hinv[tid][i]);
+            s_cam[tid][12 + i] = __float_as_uint(P->res->Mk[tid][i]);
+        }
+        s_cam[tid][9] = __float_as_uint((float)(P->cam_w[tid] - 1));
+        s_cam[tid][10] = __float_as_uint((float)(P->cam_h[tid] - 1));
+        s_cam[tid][11] = (uint32_t)P->cam_pitch[tid];
+        s_cam[tid][21] = (uint32_t)P->cam_h[tid];
+        s_cam[tid][22] = (uint32_t)(uintptr_t)P->frame[tid];
+        s_cam[tid][23] = (uint32_t)((uintptr_t)P->frame[tid] >> 32);
         s_fr[tid] = P->frame[tid];
     }
     if (tid < MAXC * MAXC) (&s_pair[0][0])[tid] = (int8_t)(&P->pair_of[0][0])[tid];
@@ -835,20 +882,19 @@ __device__ __forceinline__ void blend_body(const DevPlan* __restrict__ P, const 
     const int W = P->canvas_w, H = P->canvas_h, Wp = P->Wp;
     const bool lit = (P->readings & VS_READ_LITERAL_EQ17) != 0;
     const bool ovl_only = (P->readings & VS_READ_OVERLAP_ONLY) != 0;
-    // wavefront w takes the 64 columns [64 w, 64 w + 64) of the tile, 16 lanes
-    // of 4 pixels per row, 4 rows at a time: a wavefront's pixels lie in one
+    // wavefront w takes the 64 columns [64 (w % 4), + 64) of rows 4 (w / 4) .. + 3 of
+    // the tile, 16 lanes of 4 pixels per row: a wavefront's pixels lie in one
     // narrow band, so few of them straddle the edge of an overlap (where both
     // the one-camera and the two-camera code would run)
-    static_assert(BL_TX == 64 * (BL_THREADS / 64) && BL_TY % 4 == 0, "blend tile = 4 x 64-column bands");
-    const int xq = bx * BL_TX + (tid >> 6) * 64 + (tid & 15) * 4;
+    static_assert(BL_TX == 256 && 4 * BL_TY == 64 * (BLEND_THREADS / 64) / 16, "blend tile = 4 x 64-column bands, a row per 16 lanes");
+    const int xq = bx * BL_TX + ((tid >> 6) & 3) * 64 + (tid & 15) * 4;
     const bool vec = (W & 3) == 0;
-    // pixels whose phases run together: 1 (with the 4 codes read at once and
-    // the pair constants in LDS); 2 and 4 need 127 and 162 VGPRs and were
+    // pixels whose phases run together in the general path: 1 (with the 4 codes read
+    // at once and the pair constants in LDS); 2 and 4 need 127 and 162 VGPRs and were
     // slower (4 x 1080p blend 71 -> 78 / 92 us)
     constexpr int BG = 1;
-    for (int r = (tid & 63) >> 4; r < BL_TY; r += 4) {
-        const int y = by * BL_TY + r;
-        if (y >= H || xq >= W) continue;
+    const int y = by * BL_TY + (tid >> 8) * 4 + ((tid & 63) >> 4);
+    if (y < H && xq < W) {
         // (1) candidates: bits 0-5 and 6-11 (3 camera + shift + 1), bits 12+ their count
         uint32_t code[4];
         if (vec && xq + 3 < W) {
@@ -863,127 +909,165 @@ __device__ __forceinline__ void blend_body(const DevPlan* __restrict__ P, const 
             for (int q = 0; q < 4; ++q) code[q] = xq + q < W ? gmem(P->pix_code)[(size_t)y * W + xq + q] : 0u;
         }
         uint32_t ob[3] = {0u, 0u, 0u};
+        const uint32_t kind = code[0] >> 12;
+        const bool same = code[1] == code[0] && code[2] == code[0] && code[3] == code[0];
+        if (__all(same && kind == 1u)) {
+            // every thread's 4 pixels lie in one camera each: its constants are read
+            // once, two pixels' loads are in flight together
+            const int bit = (int)(code[0] & 63u), k = bit / 3, sh = bit % 3 - 1;
+            float h[9], M[9], wm1, hm1;
+            int pitch, Hc;
+            const uint8_t* F;
+            blend_camera(s_cam[k], h, M, wm1, hm1, pitch, Hc, F);
+            const float ru = __builtin_fmaf(h[1], (float)y, h[2]), rv = __builtin_fmaf(h[4], (float)y, h[5]);
+            const float rw = __builtin_fmaf(h[7], (float)y, h[8]);
 #pragma unroll
-        for (int g = 0; g < 4; g += BG) {
-            int nh[BG], ka[BG], kb[BG], pq[BG];
-            float th[BG], ua[BG], va[BG];
-            typedef float f2v __attribute__((ext_vector_type(2)));
-            f2v fij[BG], fji[BG];
+            for (int q0 = 0; q0 < 4; q0 += 2) {
+                BilTaps t[2];
 #pragma unroll
-            for (int q = 0; q < BG; ++q) {
-                const int x = xq + g + q;
-                nh[q] = (int)(code[g + q] >> 12);
-                ka[q] = 0;
-                kb[q] = 0;
-                pq[q] = 0;
-                th[q] = 0.0f;
-                ua[q] = 0.0f;
-                va[q] = 0.0f;
-                if (nh[q] <= 0) continue;
-                // the covering (camera, shift) candidates found at plan time, in the
-                // coverage scan's order; their positions are evaluated again
-                int hc[2] = {0, 0}, hm[2] = {0, 0};
-                float hu[2] = {0, 0}, hv[2] = {0, 0};
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    if (e >= nh[q]) break;
-                    const int bit = (int)((code[g + q] >> (6 * e)) & 63u);
-                    const int k = bit / 3, sh = bit % 3 - 1;
-                    hc[e] = k;
-                    hm[e] = sh;
-                    hom(s_hinv[k], (float)(x + sh * Wp), (float)y, s_cw[k], s_ch[k], hu[e], hv[e]);
-                }
-                if (nh[q] == 1) {
-                    ka[q] = hc[0];
-                    ua[q] = hu[0];
-                    va[q] = hv[0];
-                    continue;
-                }
-                const int p = s_pair[hc[0]][hc[1]];
-                const int ji = hc[0] == s_pj[p] ? 0 : 1;
-                const int kj = hc[ji], ki = hc[1 - ji];
-                const int mj = hm[ji], mi = hm[1 - ji];
-                float dj = fminf(hu[ji], (float)(s_cw[kj] - 1) - hu[ji]);
-                float di = fminf(hu[1 - ji], (float)(s_cw[ki] - 1) - hu[1 - ji]);
-                if (dj < 0.0f) dj = 0.0f;
-                if (di < 0.0f) di = 0.0f;
-                const float sum = di + dj;
-                th[q] = sum > 0.0f ? di / sum : 0.5f;
-                const int lx = x + mj * Wp - s_fx0[p], ly = y - s_fy0[p];
-                const size_t qf = (size_t)ly * s_fw[p] + lx;
-                fij[q] = gmem((const f2v*)s_fl[p][0])[qf];
-                fji[q] = gmem((const f2v*)s_fl[p][1])[qf];
-                ka[q] = ki;
-                kb[q] = kj;
-                pq[q] = p;
-                // the canvas columns of the two samples, shifts included
-                ua[q] = (float)(x + mi * Wp);
-                va[q] = (float)(x + mj * Wp);
-            }
-            // (2) bilinear taps: sample a (one camera, or camera i), sample b (camera j)
-            BilTaps ta[BG], tb[BG];
-#pragma unroll
-            for (int q = 0; q < BG; ++q) {
-                if (nh[q] == 1) {
-                    const int k = ka[q];
-                    bil_load(s_fr[k], s_cp[k], s_cw[k], s_ch[k], ua[q], va[q], ta[q]);
-                } else if (nh[q] >= 2) {
-                    // eq. (17): camera i moves by theta_j flow_ij, camera j by theta_i
-                    // flow_ji (as printed: theta_i and theta_j, VS_READ_LITERAL_EQ17)
-                    const float thi = th[q], thj = 1.0f - thi;
-                    const float wi = lit ? thi : thj, wj = lit ? thj : thi;
-                    const float Xi = __builtin_fmaf(wi, fij[q].x, ua[q]);
-                    const float Yi = __builtin_fmaf(wi, fij[q].y, (float)y);
-                    const float Xj = __builtin_fmaf(wj, fji[q].x, va[q]);
-                    const float Yj = __builtin_fmaf(wj, fji[q].y, (float)y);
-                    const int ki = ka[q], kj = kb[q];
+                for (int q = 0; q < 2; ++q) {
+                    const float X = (float)(xq + q0 + q + sh * Wp);
                     float u, v;
-                    hom(s_hinv[ki], Xi, Yi, s_cw[ki], s_ch[ki], u, v);
-                    bil_load(s_fr[ki], s_cp[ki], s_cw[ki], s_ch[ki], u, v, ta[q]);
-                    hom(s_hinv[kj], Xj, Yj, s_cw[kj], s_ch[kj], u, v);
-                    bil_load(s_fr[kj], s_cp[kj], s_cw[kj], s_ch[kj], u, v, tb[q]);
+                    hom_div(__builtin_fmaf(h[0], X, ru), __builtin_fmaf(h[3], X, rv), __builtin_fmaf(h[6], X, rw), u, v);
+                    bil_load(F, pitch, Hc, wm1, wm1 - 1.0f, hm1, u, v, t[q]);
                 }
-            }
-            // (3) colour correction and fusion, eq. (18)
 #pragma unroll
-            for (int q = 0; q < BG; ++q) {
-                uint32_t o0 = 0, o1 = 0, o2 = 0;
-                if (nh[q] == 1) {
+                for (int q = 0; q < 2; ++q) {
                     float s[3];
-                    bil_rgb(ta[q], s);
-                    const float* M = s_M[ka[q]];
-                    o0 = round8(capply(s, M, 0));
-                    o1 = round8(capply(s, M, 1));
-                    o2 = round8(capply(s, M, 2));
-                } else if (nh[q] >= 2) {
-                    float si[3], sj[3];
-                    bil_rgb(ta[q], si);
-                    bil_rgb(tb[q], sj);
-                    // overlap-only reading: camera i's own pair matrix (camera j's is I)
-                    const float* Mi = ovl_only ? P->res->Mpf[pq[q]] : s_M[ka[q]];
-                    const float* Mj = s_M[kb[q]];
-                    const float thi = th[q];
-                    float ti, tj;
-                    ti = capply(si, Mi, 0);
-                    tj = capply(sj, Mj, 0);
-                    o0 = round8(__builtin_fmaf(thi, ti - tj, tj));
-                    ti = capply(si, Mi, 1);
-                    tj = capply(sj, Mj, 1);
-                    o1 = round8(__builtin_fmaf(thi, ti - tj, tj));
-                    ti = capply(si, Mi, 2);
-                    tj = capply(sj, Mj, 2);
-                    o2 = round8(__builtin_fmaf(thi, ti - tj, tj));
+                    bil_rgb(t[q], s);
+#pragma unroll
+                    for (int e = 0; e < 3; ++e) {
+                        const uint32_t o = round8(capply(s, M, e));
+                        atomicAdd(&my_hist[256 * e + o], 1u);
+                        const int n3 = (q0 + q) * 3 + e;
+                        ob[n3 >> 2] |= o << (8 * (n3 & 3));
+                    }
                 }
-                if (nh[q] > 0) {
-                    atomicAdd(&my_hist[o0], 1u);
-                    atomicAdd(&my_hist[256 + o1], 1u);
-                    atomicAdd(&my_hist[512 + o2], 1u);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+#pragma unroll
+            for (int g = 0; g < 4; g += BG) {
+                int nh[BG], ka[BG], kb[BG], pq[BG];
+                float th[BG], ua[BG], va[BG];
+                typedef float f2v __attribute__((ext_vector_type(2)));
+                f2v fij[BG], fji[BG];
+#pragma unroll
+                for (int q = 0; q < BG; ++q) {
+                    const int x = xq + g + q;
+                    nh[q] = (int)(code[g + q] >> 12);
+                    ka[q] = 0;
+                    kb[q] = 0;
+                    pq[q] = 0;
+                    th[q] = 0.0f;
+                    ua[q] = 0.0f;
+                    va[q] = 0.0f;
+                    if (nh[q] <= 0) continue;
+                    // the covering (camera, shift) candidates found at plan time, in the
+                    // coverage scan's order; their positions are evaluated again
+                    int hc[2] = {0, 0}, hm[2] = {0, 0};
+                    float hu[2] = {0, 0}, hv[2] = {0, 0};
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        if (e >= nh[q]) break;
+                        const int bit = (int)((code[g + q] >> (6 * e)) & 63u);
+                        const int k = bit / 3, sh = bit % 3 - 1;
+                        hc[e] = k;
+                        hm[e] = sh;
+                        hom(s_hinv[k], (float)(x + sh * Wp), (float)y, s_cw[k], s_ch[k], hu[e], hv[e]);
+                    }
+                    if (nh[q] == 1) {
+                        ka[q] = hc[0];
+                        ua[q] = hu[0];
+                        va[q] = hv[0];
+                        continue;
+                    }
+                    const int p = s_pair[hc[0]][hc[1]];
+                    const int ji = hc[0] == s_pj[p] ? 0 : 1;
+                    const int kj = hc[ji], ki = hc[1 - ji];
+                    const int mj = hm[ji], mi = hm[1 - ji];
+                    float dj = fminf(hu[ji], (float)(s_cw[kj] - 1) - hu[ji]);
+                    float di = fminf(hu[1 - ji], (float)(s_cw[ki] - 1) - hu[1 - ji]);
+                    if (dj < 0.0f) dj = 0.0f;
+                    if (di < 0.0f) di = 0.0f;
+                    const float sum = di + dj;
+                    th[q] = sum > 0.0f ? di / sum : 0.5f;
+                    const int lx = x + mj * Wp - s_fx0[p], ly = y - s_fy0[p];
+                    const size_t qf = (size_t)ly * s_fw[p] + lx;
+                    fij[q] = gmem((const f2v*)s_fl[p][0])[qf];
+                    fji[q] = gmem((const f2v*)s_fl[p][1])[qf];
+                    ka[q] = ki;
+                    kb[q] = kj;
+                    pq[q] = p;
+                    // the canvas columns of the two samples, shifts included
+                    ua[q] = (float)(x + mi * Wp);
+                    va[q] = (float)(x + mj * Wp);
                 }
-                // byte 3 n + c of the thread's 12 output bytes (pixel n, channel c)
-                const int n3 = (g + q) * 3;
-                ob[n3 >> 2] |= o0 << (8 * (n3 & 3));
-                ob[(n3 + 1) >> 2] |= o1 << (8 * ((n3 + 1) & 3));
-                ob[(n3 + 2) >> 2] |= o2 << (8 * ((n3 + 2) & 3));
+                // (2) bilinear taps: sample a (one camera, or camera i), sample b (camera j)
+                BilTaps ta[BG], tb[BG];
+#pragma unroll
+                for (int q = 0; q < BG; ++q) {
+                    if (nh[q] == 1) {
+                        const int k = ka[q];
+                        bil_load(s_fr[k], s_cp[k], s_ch[k], s_wm1[k], s_wm1[k] - 1.0f, s_hm1[k], ua[q], va[q], ta[q]);
+                    } else if (nh[q] >= 2) {
+                        // eq. (17): camera i moves by theta_j flow_ij, camera j by theta_i
+                        // flow_ji (as printed: theta_i and theta_j, VS_READ_LITERAL_EQ17)
+                        const float thi = th[q], thj = 1.0f - thi;
+                        const float wi = lit ? thi : thj, wj = lit ? thj : thi;
+                        const float Xi = __builtin_fmaf(wi, fij[q].x, ua[q]);
+                        const float Yi = __builtin_fmaf(wi, fij[q].y, (float)y);
+                        const float Xj = __builtin_fmaf(wj, fji[q].x, va[q]);
+                        const float Yj = __builtin_fmaf(wj, fji[q].y, (float)y);
+                        const int ki = ka[q], kj = kb[q];
+                        float u, v;
+                        hom(s_hinv[ki], Xi, Yi, s_cw[ki], s_ch[ki], u, v);
+                        bil_load(s_fr[ki], s_cp[ki], s_ch[ki], s_wm1[ki], s_wm1[ki] - 1.0f, s_hm1[ki], u, v, ta[q]);
+                        hom(s_hinv[kj], Xj, Yj, s_cw[kj], s_ch[kj], u, v);
+                        bil_load(s_fr[kj], s_cp[kj], s_ch[kj], s_wm1[kj], s_wm1[kj] - 1.0f, s_hm1[kj], u, v, tb[q]);
+                    }
+                }
+                // (3) colour correction and fusion, eq. (18)
+#pragma unroll
+                for (int q = 0; q < BG; ++q) {
+                    uint32_t o0 = 0, o1 = 0, o2 = 0;
+                    if (nh[q] == 1) {
+                        float s[3];
+                        bil_rgb(ta[q], s);
+                        const float* M = s_M[ka[q]];
+                        o0 = round8(capply(s, M, 0));
+                        o1 = round8(capply(s, M, 1));
+                        o2 = round8(capply(s, M, 2));
+                    } else if (nh[q] >= 2) {
+                        float si[3], sj[3];
+                        bil_rgb(ta[q], si);
+                        bil_rgb(tb[q], sj);
+                        // overlap-only reading: camera i's own pair matrix (camera j's is I)
+                        const float* Mi = ovl_only ? P->res->Mpf[pq[q]] : s_M[ka[q]];
+                        const float* Mj = s_M[kb[q]];
+                        const float thi = th[q];
+                        float ti, tj;
+                        ti = capply(si, Mi, 0);
+                        tj = capply(sj, Mj, 0);
+                        o0 = round8(__builtin_fmaf(thi, ti - tj, tj));
+                        ti = capply(si, Mi, 1);
+                        tj = capply(sj, Mj, 1);
+                        o1 = round8(__builtin_fmaf(thi, ti - tj, tj));
+                        ti = capply(si, Mi, 2);
+                        tj = capply(sj, Mj, 2);
+                        o2 = round8(__builtin_fmaf(thi, ti - tj, tj));
+                    }
+                    if (nh[q] > 0) {
+                        atomicAdd(&my_hist[o0], 1u);
+                        atomicAdd(&my_hist[256 + o1], 1u);
+                        atomicAdd(&my_hist[512 + o2], 1u);
+                    }
+                    // byte 3 n + c of the thread's 12 output bytes (pixel n, channel c)
+                    const int n3 = (g + q) * 3;
+                    ob[n3 >> 2] |= o0 << (8 * (n3 & 3));
+                    ob[(n3 + 1) >> 2] |= o1 << (8 * ((n3 + 1) & 3));
+                    ob[(n3 + 2) >> 2] |= o2 << (8 * ((n3 + 2) & 3));
+                }
             }
         }
         uint8_t* const prow = P->pano + (size_t)y * P->pano_pitch + (size_t)xq * 3;
@@ -999,7 +1083,7 @@ __device__ __forceinline__ void blend_body(const DevPlan* __restrict__ P, const 
     }
     __syncthreads();
     uint32_t* gh = &P->acc->pano_hist[bid % PANO_SPREAD][0][0];
-    for (int i = tid; i < 3 * 256; i += BL_THREADS) {
+    for (int i = tid; i < 3 * 256; i += BLEND_THREADS) {
         uint32_t h = 0;
 #pragma unroll
         for (int k = 0; k < 8; ++k) h += s_hist[k][i];
@@ -1014,7 +1098,7 @@ __device__ __forceinline__ void blend_body(const DevPlan* __restrict__ P, const 
 // ---------------------------------------------------------------------------
 
 // Eqs. (15)-(18) over every canvas tile.
-__global__ __launch_bounds__(BL_THREADS) void k_blend(const Batch B)
+__global__ __launch_bounds__(BLEND_THREADS) void k_blend(const Batch B)
 {
     __shared__ uint32_t s_hist[8][3 * 256 + 1];
     int c;
@@ -1265,7 +1349,7 @@ hipError_t launch_blend(const Group& g, hipStream_t s)
 {
     Batch B;
     if (make_batch(g, B, [](const DevPlan& h) { return h.blend_tx * h.blend_ty; }))
-        hipLaunchKernelGGL(k_blend, dim3(B.off[B.n]), dim3(BL_THREADS), 0, s, B);
+        hipLaunchKernelGGL(k_blend, dim3(B.off[B.n]), dim3(BLEND_THREADS), 0, s, B);
     return hipGetLastError();
 }
 
