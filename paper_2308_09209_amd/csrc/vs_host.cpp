@@ -1656,23 +1656,27 @@ hipError_t flow_domain_fill(const DevPlan& d, hipStream_t s)
 hipError_t flow_run(const DevPlan& d, DevPlan* dp, const float* yt, const float* ym, float* flow_tm,
                     float* flow_mt, hipStream_t s)
 {
-    const size_t n = (size_t)d.sw[0] * d.sh[0];
     Group g;
     std::memset(&g, 0, sizeof g);
     g.n = 1;
     g.dp[0] = dp;
     g.hp[0] = &d;
-    hipError_t e = hipMemcpyAsync(d.pyr[0][0][0], yt, n * 4, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(d.pyr[0][1][0], ym, n * 4, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess) e = launch_zero(g, s);
-    for (int l = 0; l + 1 < d.levels && e == hipSuccess; ++l) e = launch_pyr_down(g, l, PYR_ALL, s);
+    hipError_t e = launch_pair_in(d, dp, yt, ym, s);
+    for (int l = 1; l + 1 < d.levels && e == hipSuccess; ++l) e = launch_pyr_down(g, l, PYR_ALL, s);
     for (int l = d.levels - 1; l >= 0 && e == hipSuccess; --l) {
         e = launch_lk(g, l, s);
         if (e == hipSuccess) e = launch_var(g, l, s);
     }
-    if (e == hipSuccess && flow_tm) e = hipMemcpyAsync(flow_tm, d.flow[0][0][0], n * 8, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess && flow_mt) e = hipMemcpyAsync(flow_mt, d.flow[0][1][0], n * 8, hipMemcpyDeviceToDevice, s);
-    return e;
+    if (e != hipSuccess || (!flow_tm && !flow_mt)) return e;
+    // (overlapping outputs: one after the other, the second's values stay)
+    const size_t bytes = (size_t)d.sw[0] * d.sh[0] * 8;
+    const uintptr_t a = (uintptr_t)flow_tm, b = (uintptr_t)flow_mt;
+    if (a && b && a < b + bytes && b < a + bytes) {
+        e = launch_pair_out(d, dp, flow_tm, nullptr, s);
+        flow_tm = nullptr;
+        if (e != hipSuccess) return e;
+    }
+    return launch_pair_out(d, dp, flow_tm, flow_mt, s);
 }
 
 }  // namespace vs

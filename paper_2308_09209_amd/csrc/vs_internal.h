@@ -193,6 +193,10 @@ hipError_t launch_plan_scan(const DevPlan* dp, const DevPlan& hp, PlanScan* scan
 hipError_t launch_need(const DevPlan* dp, const DevPlan& hp, hipStream_t s);
 hipError_t launch_set_io(const FrameIO& io, int n, int max_pairs, hipStream_t s);
 hipError_t launch_zero(const Group& g, hipStream_t s);
+// a caller's luma pair into levels 0 and 1 and the accumulators cleared; its level-0
+// flows out (either may be null)
+hipError_t launch_pair_in(const DevPlan& d, const DevPlan* dp, const float* yt, const float* ym, hipStream_t s);
+hipError_t launch_pair_out(const DevPlan& d, const DevPlan* dp, float* f0, float* f1, hipStream_t s);
 hipError_t launch_strips(const Group& g, hipStream_t s);
 hipError_t launch_lut(const Group& g, hipStream_t s);
 hipError_t launch_solve(const Group& g, hipStream_t s);

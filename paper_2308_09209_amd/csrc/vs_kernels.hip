@@ -604,7 +604,10 @@ __global__ __launch_bounds__(256) void k_pyr0(const Batch B, int skip_kept)
 
 // level l -> l + 1: separable [1 4 6 4 1] / 16, horizontal first, clamped,
 // even positions; each pass ((((a0 + 4 a1) + 6 a2) + 4 a3) + a4) / 16
-__device__ __forceinline__ void pyr_down_body(const DevPlan* __restrict__ P, const int bid, int l, int skip_kept)
+// src0, src1 (CALLER): the level's images outside the pyramid
+template <bool CALLER = false>
+__device__ __forceinline__ void pyr_down_body(const DevPlan* __restrict__ P, const int bid, int l, int skip_kept,
+                                              const float* src0 = nullptr, const float* src1 = nullptr)
 {
     const int lo = l + 1;
     const int f = find_field(P->pyr_off[lo], 2 * P->n_pairs, bid);
@@ -614,7 +617,7 @@ __device__ __forceinline__ void pyr_down_body(const DevPlan* __restrict__ P, con
     const int ws = P->lw[p][l], hs = P->lh[p][l];
     const int wd = P->lw[p][lo], hd = P->lh[p][lo];
     const int tx0 = (t % P->pyr_tx[lo][f]) * PYR_TX, ty0 = (t / P->pyr_tx[lo][f]) * PYR_TY;
-    const float* __restrict__ src = P->pyr[p][cam][l];
+    const float* __restrict__ src = CALLER ? (cam == 0 ? src0 : src1) : P->pyr[p][cam][l];
     float* __restrict__ dst = P->pyr[p][cam][lo];
     const int x = tx0 + (threadIdx.x & 63);
     const int xs[5] = {clampi(2 * x - 2, 0, ws - 1), clampi(2 * x - 1, 0, ws - 1), clampi(2 * x, 0, ws - 1),
@@ -647,6 +650,45 @@ __global__ __launch_bounds__(256) void k_pyr_down(const Batch B, int l, int skip
     int c;
     const int b = batch_block(B, blockIdx.x, c);
     pyr_down_body(B.plan[c], b, l, skip_kept);
+}
+
+// A caller's luma pair in and out.  Copies of a few MB and launches of a few us:
+// bound by the launches, so those that do not depend on each other are one.  In: the
+// pair to level 0 (n floats each), the accumulators cleared, and in the first `down`
+// blocks level 1 from the caller's images themselves.  Out: the two level-0 flows.
+// Caller pointers may have any alignment, so the 16-byte moves declare none.
+// As four library copies, the clear and the level-1 reduction (six launches) one pair
+// after the other took 151.6 us at 256 x 1080 and 70.4 at 97 x 61; so 144.5 and 63.7.
+typedef uint32_t u32x4_a1 __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t u32_a1 __attribute__((aligned(1)));
+
+// n words, thread i of m
+__device__ __forceinline__ void copy_words(void* dst, const void* src, size_t n, size_t i, size_t m)
+{
+    const size_t q = n / 4;
+    for (size_t k = i; k < q; k += m) ((u32x4_a1*)dst)[k] = ((const u32x4_a1*)src)[k];
+    if (i < n - 4 * q) ((u32_a1*)dst)[4 * q + i] = ((const u32_a1*)src)[4 * q + i];
+}
+
+__global__ __launch_bounds__(256) void k_pair_in(const DevPlan* __restrict__ P, const float* yt, const float* ym,
+                                                 size_t n, int down)
+{
+    if ((int)blockIdx.x < down) {
+        pyr_down_body<true>(P, blockIdx.x, 0, 0, yt, ym);
+        return;
+    }
+    const size_t i = (size_t)(blockIdx.x - down) * 256 + threadIdx.x, m = (size_t)(gridDim.x - down) * 256;
+    uint4* acc = (uint4*)P->acc;
+    for (size_t k = i; k < sizeof(Accum) / 16; k += m) acc[k] = make_uint4(0, 0, 0, 0);
+    copy_words(P->pyr[0][0][0], yt, n, i, m);
+    copy_words(P->pyr[0][1][0], ym, n, i, m);
+}
+
+__global__ __launch_bounds__(256) void k_pair_out(const DevPlan* __restrict__ P, float* f0, float* f1, size_t n)
+{
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x, m = (size_t)gridDim.x * 256;
+    if (f0) copy_words(f0, P->flow[0][0][0], 2 * n, i, m);
+    if (f1) copy_words(f1, P->flow[0][1][0], 2 * n, i, m);
 }
 
 // Levels 0-2 in one pass (pyramids of 3 or more levels).  A block takes a
@@ -1262,6 +1304,27 @@ hipError_t launch_zero(const Group& g, hipStream_t s)
     const int per = (int)((sizeof(Accum) / 16 + 255) / 256);
     if (make_batch(g, B, [&](const DevPlan&) { return per; }))
         hipLaunchKernelGGL(k_zero, dim3(B.off[B.n]), dim3(256), 0, s, B);
+    return hipGetLastError();
+}
+
+// blocks of a copy of n words: one 16-byte move per thread up to four blocks per CU
+static int copy_blocks(size_t n)
+{
+    return (int)std::min<size_t>(1024, std::max<size_t>(1, (n / 4 + 255) / 256));
+}
+
+hipError_t launch_pair_in(const DevPlan& d, const DevPlan* dp, const float* yt, const float* ym, hipStream_t s)
+{
+    const size_t n = (size_t)d.sw[0] * d.sh[0];
+    const int down = d.levels > 1 ? d.pyr_off[1][2] : 0;
+    hipLaunchKernelGGL(k_pair_in, dim3(down + copy_blocks(n)), dim3(256), 0, s, dp, yt, ym, n, down);
+    return hipGetLastError();
+}
+
+hipError_t launch_pair_out(const DevPlan& d, const DevPlan* dp, float* f0, float* f1, hipStream_t s)
+{
+    const size_t n = (size_t)d.sw[0] * d.sh[0];
+    hipLaunchKernelGGL(k_pair_out, dim3(copy_blocks(2 * n)), dim3(256), 0, s, dp, f0, f1, n);
     return hipGetLastError();
 }
 

@@ -292,6 +292,37 @@ def test_flow_forms_by_level_size_match_oracle(w, h, scale, lam, iters):
     np.testing.assert_array_equal(b.cpu().numpy(), O.pyramid_flow(pyr(M), pyr(T), iters=iters, lam=lf))
 
 
+@pytest.mark.parametrize("w,h,levels,off", [(5, 3, 1, 0), (17, 9, 2, 1), (64, 16, 4, 2), (129, 33, 4, 3), (1500, 801, 3, 1)])
+def test_pair_in_and_out(w, h, levels, off):
+    """A luma pair at any word alignment, sizes with and without remainders of the
+    copies' words, one level and several, twice on one context: levels 0 and 1 and the
+    two flows are the ones of aligned images and of the oracle, words outside the
+    outputs stay, and outputs may be left out."""
+    rng = np.random.default_rng(w)
+    pf = V.PlainFlow(w, h, lk_levels=levels)
+    say(f"[pair {w}x{h}] levels {levels} offset {off}")
+    for _ in range(2):
+        T, M = (rng.integers(0, 256, (h, w)).astype(np.float32) for _ in range(2))
+        want = [t.cpu().numpy().ravel() for t in pf(torch.from_numpy(T).cuda(), torch.from_numpy(M).cuda())]
+        src = [torch.zeros(h * w + 8, device="cuda") for _ in range(2)]
+        for buf, a in zip(src, (T, M)):
+            buf[off:off + h * w] = torch.from_numpy(a.ravel()).cuda()
+        for use in ((1, 1), (1, 0), (0, 1)):
+            dst = [torch.full((2 * h * w + 8,), -7.0, device="cuda") for _ in range(2)]
+            ptr = [V._p(d[off:]) if u else None for d, u in zip(dst, use)]
+            V.check(V.lib().vs_flow_run(pf.hnd, V._p(src[0][off:]), V._p(src[1][off:]), *ptr, V._stream_handle(None)),
+                    "vs_flow_run")
+            for d, u, f in zip(dst, use, want):
+                got = d.cpu().numpy()
+                out = np.full_like(got, -7.0)
+                if u:
+                    out[off:off + 2 * h * w] = f
+                np.testing.assert_array_equal(got, out)
+        for l in range(min(levels, 2)):
+            for got, a in zip(pf.level(l), (T, M)):
+                np.testing.assert_array_equal(got.cpu().numpy(), a if l == 0 else O.pyr_down(a))
+
+
 @pytest.mark.parametrize("rows", [8, 16])
 def test_fused_pyramid_tile_heights(rows):
     """levels 0-2 in one pass at either level-2 tile height: every pyramid
