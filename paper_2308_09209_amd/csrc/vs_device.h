@@ -99,22 +99,6 @@ __device__ __forceinline__ bool hom(const float* __restrict__ h, float x, float 
     return (u >= 0.0f) && (u <= (float)(W - 1)) && (v >= 0.0f) && (v <= (float)(H - 1));
 }
 
-// the position alone, and its u alone
-__device__ __forceinline__ void hom_pos(const float* __restrict__ h, float x, float y, float& u, float& v)
-{
-    hom_div(__builtin_fmaf(h[0], x, __builtin_fmaf(h[1], y, h[2])), __builtin_fmaf(h[3], x, __builtin_fmaf(h[4], y, h[5])),
-            __builtin_fmaf(h[6], x, __builtin_fmaf(h[7], y, h[8])), u, v);
-}
-
-__device__ __forceinline__ float hom_u(const float* __restrict__ h, float x, float y)
-{
-    const float nu = __builtin_fmaf(h[0], x, __builtin_fmaf(h[1], y, h[2]));
-    const float w = __builtin_fmaf(h[6], x, __builtin_fmaf(h[7], y, h[8]));
-    const bool safe = w >= DIV_LO && fmaxf(fabsf(nu), w) <= DIV_HI && fabsf(nu) >= 0x1p-60f;
-    if (__any(!safe)) return w > 0.0f ? nu / w : 0.0f;
-    return div_by(nu, w, div_rcp(w));
-}
-
 // a pointer into device (global) memory as such: its loads and stores become
 // global_* instructions, which count against the vector-memory counter only
 // (flat ones also hold back the waits of LDS operations)
