@@ -26,14 +26,19 @@ __device__ __forceinline__ uint32_t round8(float r)
     return (uint32_t)(int)__builtin_amdgcn_fmed3f(r + 0.5f, 0.0f, 255.0f);
 }
 
-// Quotients, correctly rounded (the same bits as the division operator): the reciprocal y of d, itself correctly rounded, then for each
-// numerator q = n y and twice the remainder step q + (n - q d) y, the second from a
-// quotient within one unit in the last place, which rounds correctly (Markstein,
-// "Computation of elementary functions on the IBM RISC System/6000", 1990).
+// Quotients, correctly rounded (the same bits as the division operator): the
+// reciprocal y of d, itself correctly rounded, then for each numerator q = n y and
+// twice the remainder step q + (n - q d) y, the second from a quotient within one unit
+// in the last place, which rounds correctly (Markstein, "Computation of elementary
+// functions on the IBM RISC System/6000", 1990).  That y is correctly rounded rests on
+// the hardware's estimate (a step from one below 1/d would miss the all-ones
+// significand): every float of [DIV_LO, DIV_HI] is compared with the operator by
+// tests/test_gpu_math.py, quotients next to rounding midpoints with IEEE's.
 // No intermediate leaves the normal range for d in [DIV_LO, DIV_HI] and numerators
 // that are 0 or between 2^-60 and 2^60 in magnitude.  The remainder is formed
-// negated, so that zeros keep their sign.  20 plain multiplications and additions
-// where the two operators take 40 instructions, half of them at the half rate.
+// negated, so that zeros keep their sign.  13 instructions for two
+// quotients, the estimate among them and the range test besides, where the two
+// operators take 40, half of them at the half rate.
 constexpr float DIV_LO = 0x1p-40f, DIV_HI = 0x1p60f;
 
 __device__ __forceinline__ float div_rcp(float d)
@@ -56,8 +61,8 @@ __device__ __forceinline__ float div_by(float n, float d, float y)
 }
 
 // 0.5 / sqrt(x), both correctly rounded, for x in [2^-100, 2^100]: the root from the
-// hardware's reciprocal root and one remainder step (every float of that range from
-// 2^-8 up checked against the operator), then its reciprocal as above.
+// hardware's reciprocal root and one remainder step, then its reciprocal as above (every
+// float of that range compared with the operators by tests/test_gpu_math.py).
 __device__ __forceinline__ float half_rsqrt(float x)
 {
     const float y = __builtin_amdgcn_rsqf(x);
