@@ -406,7 +406,8 @@ vs_status vs_nn_create(const vs_nn_spec* spec, uint64_t seed, vs_nn** out);
 vs_status vs_nn_destroy(vs_nn* n);
 /* Forward over the images of imgs (back to back, NHWC): x [pixels][16] BF16
  * (device, 16-byte aligned; it must stay unchanged until the matching
- * vs_nn_backward); pred (device, may be NULL) receives the FP32 output
+ * vs_nn_backward); pred (device, may be NULL; by a copy where it is not
+ * 16-byte aligned memory of the current device) receives the FP32 output
  * [pixels][16].  The activations stay in the object for the backward pass. */
 vs_status vs_nn_forward(vs_nn* n, const uint16_t* x, const vs_nn_images* imgs, float* pred, void* stream);
 /* Sum over the last forward's pixels of the end-point error
@@ -497,7 +498,10 @@ vs_status vs_calib_estimate(const uint8_t* frame_a, int pitch_a, int wa, int ha,
  * for w x h luma images; vs_flow_run computes, on the whole image, the
  * pyramidal flow of vs_stitch for template yt and moving ym (P_m(x + f) ~
  * P_t(x)) into flow_tm and the reverse flow into flow_mt (FP32 [h][w][2],
- * either may be NULL).  Inputs and outputs are device pointers. */
+ * either may be NULL).  Inputs and outputs are device pointers of any
+ * alignment; a buffer that is not memory of the current device (another
+ * device's, host memory) goes through a copy of the runtime instead of the
+ * kernels that read and write the others where they lie. */
 typedef struct vs_flow vs_flow;
 vs_status vs_flow_create(int w, int h, const vs_params* p, vs_flow** out);
 vs_status vs_flow_run(vs_flow* f, const float* yt, const float* ym, float* flow_tm, float* flow_mt, void* stream);

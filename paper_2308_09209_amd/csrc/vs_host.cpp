@@ -10,6 +10,7 @@
 #include <string>
 #include <vector>
 
+#include "vs_caller.h"
 #include "vs_internal.h"
 
 using namespace vs;
@@ -1661,22 +1662,35 @@ hipError_t flow_run(const DevPlan& d, DevPlan* dp, const float* yt, const float*
     g.n = 1;
     g.dp[0] = dp;
     g.hp[0] = &d;
-    hipError_t e = launch_pair_in(d, dp, yt, ym, s);
+    const size_t n = (size_t)d.sw[0] * d.sh[0];
+    hipError_t e;
+    if (kernel_reaches(yt, n * 4) && kernel_reaches(ym, n * 4)) {
+        e = launch_pair_in(d, dp, yt, ym, s);
+    } else {
+        e = hipMemcpyAsync(d.pyr[0][0][0], yt, n * 4, hipMemcpyDefault, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(d.pyr[0][1][0], ym, n * 4, hipMemcpyDefault, s);
+        if (e == hipSuccess) e = launch_zero(g, s);
+        if (e == hipSuccess && d.levels > 1) e = launch_pyr_down(g, 0, PYR_ALL, s);
+    }
     for (int l = 1; l + 1 < d.levels && e == hipSuccess; ++l) e = launch_pyr_down(g, l, PYR_ALL, s);
     for (int l = d.levels - 1; l >= 0 && e == hipSuccess; --l) {
         e = launch_lk(g, l, s);
         if (e == hipSuccess) e = launch_var(g, l, s);
     }
     if (e != hipSuccess || (!flow_tm && !flow_mt)) return e;
-    // (overlapping outputs: one after the other, the second's values stay)
-    const size_t bytes = (size_t)d.sw[0] * d.sh[0] * 8;
+    const size_t bytes = n * 8;
     const uintptr_t a = (uintptr_t)flow_tm, b = (uintptr_t)flow_mt;
-    if (a && b && a < b + bytes && b < a + bytes) {
-        e = launch_pair_out(d, dp, flow_tm, nullptr, s);
-        flow_tm = nullptr;
-        if (e != hipSuccess) return e;
+    const bool direct[2] = {kernel_reaches(flow_tm, bytes), kernel_reaches(flow_mt, bytes)};
+    if ((direct[0] || !a) && (direct[1] || !b) && !(a && b && a < b + bytes && b < a + bytes))
+        return launch_pair_out(d, dp, flow_tm, flow_mt, s);
+    // one after the other: where the outputs overlap the second's values stay
+    float* const out[2] = {flow_tm, flow_mt};
+    for (int k = 0; k < 2 && e == hipSuccess; ++k) {
+        if (!out[k]) continue;
+        e = direct[k] ? launch_pair_out(d, dp, k == 0 ? out[0] : nullptr, k == 1 ? out[1] : nullptr, s)
+                      : hipMemcpyAsync(out[k], d.flow[0][k][0], bytes, hipMemcpyDefault, s);
     }
-    return launch_pair_out(d, dp, flow_tm, flow_mt, s);
+    return e;
 }
 
 }  // namespace vs

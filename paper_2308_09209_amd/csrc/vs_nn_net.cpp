@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/vstitch.h"
+#include "vs_caller.h"
 #include "vs_nn.h"
 
 using namespace vs;
@@ -234,14 +235,14 @@ vs_status vs_nn_forward(vs_nn* n, const uint16_t* x, const vs_nn_images* imgs, f
         h = n->hid[l];
     }
     const int ci = n->spec.cin[L - 1], co = n->spec.cout[L - 1];
-    // the caller's copy straight from the last layer where its stores may be
+    // the caller's copy straight from the last layer where its kernel may store there,
     // 16 bytes wide
-    const bool both = pred && (uintptr_t)pred % 16 == 0;
+    const bool both = pred && (uintptr_t)pred % 16 == 0 && kernel_reaches(pred, (size_t)npix * co * 4);
     if (e == hipSuccess)
         e = nn::conv3x3(h, ci, n->w16[L - 1], n->params + n->off[L - 1] + (size_t)co * 9 * ci, n->pred, co, T,
                         nn::CONV_F32, n->spec.alpha, s, both ? pred : nullptr);
     if (e == hipSuccess && pred && !both)
-        e = hipMemcpyAsync(pred, n->pred, (size_t)npix * co * 4, hipMemcpyDeviceToDevice, s);
+        e = hipMemcpyAsync(pred, n->pred, (size_t)npix * co * 4, hipMemcpyDefault, s);
     if (e != hipSuccess) return st(e);
     n->x = x;
     n->T = T;
