@@ -265,6 +265,7 @@ def test_deferred_flow_pixels_match_oracle():
         st.close()
 
 
+# (the last line's level 0: 1 px per thread, but 601 x 700: 3; 2 and 4 in the test after it)
 @pytest.mark.parametrize("w,h,scale,lam,iters", [
     (2, 2, 1.0, 256.0, 5), (17, 5, 1.0, 256.0, 5), (64, 117, 1.0, 1e-3, 6), (120, 125, 1.0, 256.0, 5),   # 4 lanes
     (65, 33, 1e-22, 256.0, 5), (65, 33, 1e12, 1e-12, 5), (97, 61, 1.0, 256.0, 1),      # the plain division
@@ -290,6 +291,33 @@ def test_flow_forms_by_level_size_match_oracle(w, h, scale, lam, iters):
     lf = np.float32(lam)
     np.testing.assert_array_equal(a.cpu().numpy(), O.pyramid_flow(pyr(T), pyr(M), iters=iters, lam=lf))
     np.testing.assert_array_equal(b.cpu().numpy(), O.pyramid_flow(pyr(M), pyr(T), iters=iters, lam=lf))
+
+
+@pytest.mark.parametrize("w,h,px", [(641, 380, 2), (601, 420, 2), (705, 600, 3), (1001, 529, 4)])
+@pytest.mark.parametrize("scale,lam", [(1.0, 1e-3), (1.0, 256.0), (1e-22, 256.0), (1e12, 1e-12), ("stripes", 256.0)])
+def test_flow_forms_of_2_to_4_px_per_thread_match_oracle(w, h, px, scale, lam):
+    """The default forms with 2, 3 and 4 pixels per thread at level 0 (from 512, 768 and
+    1024 tiles of 64 x 16 pixels of both fields): deferred pixels, lumas whose quotients
+    the shortened division does not take, and stripes of such lumas beside ordinary ones in
+    one wavefront; both flows bit for bit against the oracle."""
+    n16 = 2 * -(-w // 64) * -(-h // 16)
+    assert px == (4 if n16 >= 1024 else 3 if n16 >= 768 else 2) and n16 >= 512
+    rng = np.random.default_rng(w + h)
+    T = np.clip(np.cumsum(rng.normal(size=(h, w)), axis=1) * 12 + 128, 0, 255).round().astype(np.float32)
+    M = np.clip(np.roll(T, (1, 2), axis=(0, 1)) + rng.normal(size=T.shape) * 3, 0, 255).round().astype(np.float32)
+    k = np.where(np.arange(w) // 24 % 2, 1e-22, 1.0) if scale == "stripes" else scale
+    T, M = ((a * np.float32(1) * k).astype(np.float32) for a in (T, M))
+
+    def pyr(a):
+        out = [a]
+        for _ in range(3):
+            out.append(O.pyr_down(out[-1]))
+        return out
+    say(f"[flow {w}x{h}, {px} px per thread] scale {scale} lambda {lam}")
+    a, b = V.PlainFlow(w, h, lk_lambda=lam)(torch.from_numpy(T).cuda(), torch.from_numpy(M).cuda())
+    it, lf = V.default_params().lk_iters, np.float32(lam)
+    np.testing.assert_array_equal(a.cpu().numpy(), O.pyramid_flow(pyr(T), pyr(M), iters=it, lam=lf))
+    np.testing.assert_array_equal(b.cpu().numpy(), O.pyramid_flow(pyr(M), pyr(T), iters=it, lam=lf))
 
 
 @pytest.mark.parametrize("w,h,levels,off", [(5, 3, 1, 0), (17, 9, 2, 1), (64, 16, 4, 2), (129, 33, 4, 3), (1500, 801, 3, 1)])
