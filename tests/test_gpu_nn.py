@@ -216,6 +216,37 @@ def test_weight_gradient_at_unit_edges(cin, cout, sizes):
     assert (np.abs(outs[0] - ref) <= (P + 1) * u / (1 - (P + 1) * u) * mag).all()
 
 
+@pytest.mark.parametrize("cin,cout", [(16, 32), (32, 32), (32, 16)])
+@pytest.mark.parametrize("sizes", [[(256, 256)], [(257, 256)], [(512, 256)], [(513, 256)], [(700, 400)],
+                                   [(300, 211), (7, 5), (300, 211), (1, 700), (129, 300), (300, 211)]])
+def test_weight_gradient_of_many_units_is_exact(cin, cout, sizes):
+    """256, 257, 512, 513 and over 512 units of 256 pixels, of one image and of several
+    (blocks that walk several units, in one image and across images; one to five rounds of
+    the ordered sum): operands 0 to 3, so every partial sum stays below 2^24 and every
+    gradient is a whole number, held exactly"""
+    rng = np.random.default_rng(cin + cout + len(sizes))
+    P = sum(h * w for h, w in sizes)
+    assert 9 * P < 1 << 24
+    xi, zi = rng.integers(0, 4, (P, cin)), rng.integers(0, 4, (P, cout))
+    xd, zd = dev(to_bf16(xi)), dev(to_bf16(zi))
+    imgs = V.nn_images(sizes)
+    say(f"[wgrad {cin}->{cout}] {len(sizes)} images, {sum(-(-h * w // 256) for h, w in sizes)} units")
+    nbytes = V.lib().vs_nn_wgrad_scratch_bytes(cin, cout, C.byref(imgs))
+    scratch = torch.empty(nbytes // 4, dtype=torch.float32, device="cuda:0")
+    dwb = torch.empty(cout * 9 * cin + cout, dtype=torch.float32, device="cuda:0")
+    V.check(V.lib().vs_nn_conv3x3_wgrad(C.c_void_p(xd.data_ptr()), cin, C.c_void_p(zd.data_ptr()), cout,
+                                        C.byref(imgs), C.c_void_p(scratch.data_ptr()), nbytes,
+                                        C.c_void_p(dwb.data_ptr()), None), "wgrad")
+    ref, off = np.zeros(cout * 9 * cin + cout), 0
+    for h, w in sizes:
+        dw, db = O.conv3x3_bwd_weight(xi[off:off + h * w].reshape(1, h, w, cin).astype(np.float64),
+                                      zi[off:off + h * w].reshape(1, h, w, cout).astype(np.float64))
+        ref += np.concatenate([dw.reshape(-1), db.reshape(-1)])
+        off += h * w
+    assert (ref > P).all()
+    np.testing.assert_array_equal(dwb.cpu().numpy().astype(np.float64), ref)
+
+
 def test_loss_lrelu_adam_kernels():
     rng = np.random.default_rng(5)
     P = 1000
