@@ -452,6 +452,112 @@ def test_network_adam_save_load():
     V.lib().vs_nn_destroy(h2)
 
 
+def _steps(layers, sizes, steps, seed):
+    """A network of these layers after some Adam steps, with a forward and a backward
+    since: (handle, input, labels, images, max pixels)"""
+    rng = np.random.default_rng(seed)
+    P = sum(a * b for a, b in sizes)
+    spec = V.nn_spec(layers, in_live=2, alpha=0.1, max_pixels=P)
+    h = C.c_void_p()
+    V.check(V.lib().vs_nn_create(C.byref(spec), seed, C.byref(h)), "vs_nn_create")
+    x, lab, imgs = dev(to_bf16(rng.normal(size=(P, 16)))), dev(rng.normal(size=(P, 2)).astype(np.float32)), V.nn_images(sizes)
+    for t in range(steps + 1):
+        V.check(V.lib().vs_nn_forward(h, C.c_void_p(x.data_ptr()), C.byref(imgs), None, None), "fwd")
+        V.check(V.lib().vs_nn_backward(h, C.c_void_p(lab.data_ptr()), None, None), "bwd")
+        if t < steps:
+            V.check(V.lib().vs_nn_adam_step(h, 1e-2, 0.9, 0.999, 1e-8, None), "adam")
+    return h, x, lab, imgs, spec
+
+
+def _flat(h):
+    """(parameters, gradients) of network object h as FP32 bits, layer by layer"""
+    n = C.c_size_t()
+    V.check(V.lib().vs_nn_params(h, None, None, C.byref(n), None), "params count")
+    p, g = (torch.empty(n.value, dtype=torch.float32, device="cuda:0") for _ in range(2))
+    V.check(V.lib().vs_nn_params(h, C.c_void_p(p.data_ptr()), C.c_void_p(g.data_ptr()), None, None), "params")
+    torch.cuda.synchronize()
+    return p.cpu().numpy(), g.cpu().numpy()
+
+
+STEP_NETS = [(NET_LAYERS, [(23, 41), (16, 16), (5, 70)]), (S.LAYERS, [(64, 270), (33, 17)]), (((16, 32), (32, 16)), [(1, 1)])]
+
+
+@pytest.mark.parametrize("layers,sizes", STEP_NETS)
+@pytest.mark.parametrize("steps", [1, 3])
+def test_adam_step_refreshes_forward_and_transposed_weights(layers, sizes, steps):
+    """After Adam steps the BF16 weights that the forward pass reads and their flipped
+    transposes that the data gradient reads are those of the master weights: a second
+    network that loads the saved file (each copy rebuilt from the weights by the loader)
+    gives the same gradients of every layer, bit for bit."""
+    h, x, lab, imgs, spec = _steps(layers, sizes, steps, 21)
+    n = C.c_size_t()
+    V.check(V.lib().vs_nn_save(h, None, 0, C.byref(n)), "size")
+    buf = C.create_string_buffer(n.value)
+    V.check(V.lib().vs_nn_save(h, buf, n.value, C.byref(n)), "save")
+    h2 = C.c_void_p()
+    V.check(V.lib().vs_nn_create(C.byref(spec), 77, C.byref(h2)), "vs_nn_create")
+    V.check(V.lib().vs_nn_load(h2, buf.raw, n.value), "load")
+    say(f"[adam step] {len(layers)} layers, {sizes}, {steps} steps")
+    V.check(V.lib().vs_nn_forward(h2, C.c_void_p(x.data_ptr()), C.byref(imgs), None, None), "fwd")
+    V.check(V.lib().vs_nn_backward(h2, C.c_void_p(lab.data_ptr()), None, None), "bwd")
+    (p, g), (p2, g2) = _flat(h), _flat(h2)
+    off = 0
+    for ci, co in layers:
+        nw = co * 9 * ci
+        np.testing.assert_array_equal(to_bf16(p[off:off + nw]), to_bf16(p2[off:off + nw]))
+        assert np.abs(g[off:off + nw]).max() > 0
+        np.testing.assert_array_equal(g[off:off + nw + co].view(np.uint32), g2[off:off + nw + co].view(np.uint32))
+        off += nw + co
+    V.lib().vs_nn_destroy(h)
+    V.lib().vs_nn_destroy(h2)
+
+
+@pytest.mark.parametrize("layers,sizes", STEP_NETS)
+def test_network_backward_is_its_layers_calls(layers, sizes):
+    """The network's backward (the activation's derivative inside the data gradient) is,
+    bit for bit, the public calls one after the other: the loss gradient, per layer the
+    weight gradient, the plain convolution with the flipped weights, the activation's
+    backward."""
+    h, x, lab, imgs, _ = _steps(layers, sizes, 2, 22)
+    p, g = _flat(h)
+    P = x.shape[0]
+
+    def bf(n, c):
+        return torch.empty((n, c), dtype=torch.int16, device="cuda:0")
+    ws, bs, hid, offs, off = [], [], [x], [], 0
+    for l, (ci, co) in enumerate(layers):
+        nw = co * 9 * ci
+        ws.append(dev(to_bf16(p[off:off + nw])))
+        bs.append(dev(p[off + nw:off + nw + co]))
+        offs.append(off)
+        off += nw + co
+        last = l + 1 == len(layers)
+        y = torch.empty((P, co), dtype=torch.float32, device="cuda:0") if last else bf(P, co)
+        V.check(conv_call(hid[-1], ci, ws[-1], bs[-1], y, co, imgs, V.CONV_F32 if last else V.CONV_LRELU), "conv")
+        hid.append(y)
+    say(f"[network backward] {len(layers)} layers, {sizes}")
+    _, dz = S.loss_and_grad(hid[-1], lab)
+    for l in range(len(layers) - 1, -1, -1):
+        ci, co = layers[l]
+        nbytes = V.lib().vs_nn_wgrad_scratch_bytes(ci, co, C.byref(imgs))
+        scratch = torch.empty(nbytes // 4, dtype=torch.float32, device="cuda:0")
+        n = co * 9 * ci + co
+        dwb = torch.empty(n, dtype=torch.float32, device="cuda:0")
+        V.check(V.lib().vs_nn_conv3x3_wgrad(C.c_void_p(hid[l].data_ptr()), ci, C.c_void_p(dz.data_ptr()), co,
+                                            C.byref(imgs), C.c_void_p(scratch.data_ptr()), nbytes,
+                                            C.c_void_p(dwb.data_ptr()), None), "wgrad")
+        np.testing.assert_array_equal(dwb.cpu().numpy().view(np.uint32), g[offs[l]:offs[l] + n].view(np.uint32))
+        if l == 0:
+            break
+        wf, dh, nz = bf(ci * 9, co), bf(P, ci), bf(P, ci)
+        V.check(V.lib().vs_nn_flip_weights(C.c_void_p(ws[l].data_ptr()), C.c_void_p(wf.data_ptr()), ci, co, None), "flip")
+        V.check(conv_call(dz, co, wf, None, dh, ci, imgs, V.CONV_LINEAR), "dgrad")
+        V.check(V.lib().vs_nn_lrelu_bwd(C.c_void_p(dh.data_ptr()), C.c_void_p(hid[l].data_ptr()),
+                                        C.c_void_p(nz.data_ptr()), P * ci, 0.1, None), "lrelu")
+        dz = nz
+    V.lib().vs_nn_destroy(h)
+
+
 def test_pool_flow_block_means():
     """vs_nn_pool_flow against block means written out in numpy (ragged last
     block row and column) for factors 1, 3 and 4."""
