@@ -265,7 +265,7 @@ vs_status vs_get_timing(vs_ctx* c, double ms[6], uint32_t* frames);
  * vs_create picks one per level; the autotuner below measures them. */
 #define VS_FLOW_ALT 8
 #define VS_FLOW_INBLOCK 16
-#define VS_FLOW_VARIANTS 12  /* variants the autotuner measures: 1, 2, 3, 4, 9, 10, 11, 12, 25, 26, 27, 28 */
+#define VS_FLOW_VARIANTS 12  /* variants the autotuner reports: 1, 2, 3, 4, 9, 10, 11, 12, 25, 26, 27, 28 */
 vs_status vs_set_flow_variant(vs_ctx* c, int level, int variant);
 vs_status vs_get_flow_variant(const vs_ctx* c, int32_t variant[VS_MAX_LEVELS]);
 
@@ -287,9 +287,10 @@ const char* vs_batch_last_error(const vs_batch* b);
 
 /* Autotuner: for every pyramid level, run the batch on the given frames with
  * each 9x9 flow-kernel variant (1, 2, 3, 4, 9, 10, 11, 12, 25, 26, 27, 28),
- * `reps` timed runs each, and keep the fastest.  ms[l][i] receives the mean
- * frame time of the i-th of those variants at level l (may be NULL);
- * choice[l] the variant kept.  Then, with 3 or more levels, the fused
+ * `reps` timed runs each, and keep the fastest.  9 to 12 run the kernels of
+ * 1 to 4: these are timed once, and 9 to 12 get their times and are not
+ * chosen.  ms[l][i] receives the mean frame time of the i-th of those
+ * variants at level l (may be NULL); choice[l] the variant kept.  Then, with 3 or more levels, the fused
  * pyramid's tile height (8 or 16 level-2 rows) the same way.  Every context's
  * choice is recorded in the tuning records (vs_tune_put).
  * The colour states are restored afterwards.  Synchronous. */

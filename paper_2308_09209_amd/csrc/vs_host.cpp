@@ -1476,6 +1476,11 @@ vs_status vs_batch_autotune(vs_batch* b, const uint8_t* const* const frames[], u
         float best = 1e30f;
         int best_v = b->ctx[0]->hp.lk_P[l];
         for (int vi = 0; vi < VS_FLOW_VARIANTS && st == VS_OK; ++vi) {
+            // 9 - 12 launch the kernels of 1 - 4 (launch_lk): their times, no choice of theirs
+            if (variants[vi] >= 1 + VS_FLOW_ALT && variants[vi] <= 4 + VS_FLOW_ALT) {
+                if (ms_out) ms_out[l][vi] = ms_out[l][vi - 4];
+                continue;
+            }
             st = set_variant_all(b, l, variants[vi]);
             if (st == VS_OK) st = capture(b);
             if (st != VS_OK) break;

@@ -98,6 +98,23 @@ def test_batch_autotune_keeps_results():
     V.tune_clear()   # the records of this test's rigs do not reach later tests
 
 
+def test_autotune_times_each_kernel_once():
+    """variants 9 to 12 run the kernels of 1 to 4: they are given those times and are
+    never the choice"""
+    scs = scenes()[:1]
+    st = V.Stitcher(scs[0].rig())
+    b = V.Batch([st])
+    choice, ms = b.autotune([dev(scs[0].frames(0))], [st.new_pano()], reps=1)
+    say(f"[autotune] choice per level {choice}")
+    code = list(V.FLOW_VARIANT_CODES)
+    for v in (1, 2, 3, 4):
+        np.testing.assert_array_equal(ms[:, code.index(v + 8)], ms[:, code.index(v)])
+    assert (ms > 0).all() and not any(9 <= c <= 12 for c in choice)
+    b.close()
+    st.close()
+    V.tune_clear()
+
+
 def test_autotune_records_apply_to_new_contexts(tmp_path):
     """vs_batch_autotune records each context's choice (flow variants and the
     fused pyramid's tile height); a context created later for the same device
