@@ -494,29 +494,34 @@ def conv_rate(V, H=1080, W=256, N=8, K=20):
 
 
 def var_bytes_per_frame(info, outer, inner):
-    """Algorithmic HBM bytes of the variational flow step per frame: per level
-    and pair, with n the field's pixels: derivatives 2 cameras x (4 read + 20
-    written), initialisation 2 directions x (8 written + 2 read), each warp 2 x
-    (U 8, the moving image and its 5 derivative planes 24, T 4 and its 2
-    gradient planes 8, coefficients 32 and increments 8 written; + 16 to fold
-    the previous increments after the first), each Jacobi step 2 x (coefficients
-    32, U 8, increments 8 and the domain mask 1 read, increments 8 written),
-    the last fold 2 x 24."""
+    """HBM bytes of the variational flow step per frame, each launch's inputs
+    read once and outputs written once: per level and pair, with n the field's
+    pixels: derivatives 2 cameras x (4 read + 20 written); per direction each
+    warp (the moving image and its 5 derivative planes 24, T 4 and its 2
+    gradient planes 8 read, the flow 8 and coefficients 32 written; the first
+    reads the coarser level's flow and increments, 16 B per pixel there, later
+    ones the flow 8 and increments 8), each launch of two Jacobi steps
+    (coefficients 32, flow 8, domain mask 1 and, after a warp's first,
+    increments 8 read, increments 8 written), at level 0 the last fold 24.
+    Without warps each level's start is 8 written and 2 read; without steps a
+    warp writes the increments 8."""
     total = 0
     for p in range(info.n_pairs):
         w, h = int(info.strip_w[p]), int(info.strip_h[p])
         for l in range(info.lk_levels):
             n = w * h
             w, h = (w + 1) // 2, (h + 1) // 2
-            warps = sum(84 + (16 if o > 0 else 0) for o in range(outer))
-            total += n * (2 * 24 + 2 * 10 + 2 * warps + 2 * outer * inner * 57 + 2 * 24)
+            coarser = w * h if l + 1 < info.lk_levels else 0
+            steps = 57 * (inner // 2) - 8 if inner else 8
+            per_dir = outer * (76 + steps) + max(outer - 1, 0) * 16 + (24 if l == 0 and outer else 0)
+            total += 2 * n * (24 + per_dir) + 2 * 16 * coarser * (1 if outer else 0) + (0 if outer else 2 * 10 * n)
     return total
 
 
 def variational_leg(args, V, rig, frames, st_plain, H, W, mpix_plain):
     """The same frames with the variational flow alternative (flow = 2):
     throughput, latency, its flows' end-point error against the plain
-    path's, and the flow step's rate against HBM on its algorithmic bytes."""
+    path's, and the flow step's rate against HBM on its launches' bytes."""
     sv = V.Stitcher(rig, flow=2)
     pano = sv.new_pano()
     ref = V.Stitcher(rig)
@@ -549,9 +554,9 @@ def variational_leg(args, V, rig, frames, st_plain, H, W, mpix_plain):
                              achieved=round(vb / (flow_ms * 1e-3) / 1e9, 1), peak=HBM_PEAK_GBS, unit="GB/s",
                              frac=round(vb / (flow_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4), traffic=None,
                              bytes_per_frame=vb,
-                             unit_bytes="per level and field pixel: derivatives, initialisation, warps and "
-                                        "Jacobi steps (57 B each: coefficients, flow, increments, mask read; "
-                                        "increments written), fold"))
+                             unit_bytes="per level and field pixel: derivatives, warps and launches of two Jacobi "
+                                        "steps (57 B each: coefficients, flow, increments, mask read; "
+                                        "increments written), fold at level 0"))
     sv.close()
     return out
 

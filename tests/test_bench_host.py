@@ -93,3 +93,35 @@ def test_cpu_baseline_columns_group_as_the_papers_step_table():
     assert t["table4_ms"] == dict(geometric_warping=500.0, color_correction=355.0, local_warping=3150.0,
                                   image_blending=1000.0)
     assert t["step_ms"]["flow"] == 3000.0
+
+
+@pytest.mark.parametrize("outer,inner", [(3, 10), (1, 2), (2, 0), (0, 10)])
+def test_variational_bytes_launch_by_launch(outer, inner):
+    """the variational step's bytes against a walk over its launches: derivatives, then per
+    level the start and warps, a Jacobi launch per two steps, the fold at level 0"""
+    class Info:
+        n_pairs, lk_levels, strip_w, strip_h = 2, 3, [37, 64], [20, 5]
+    want = 0
+    for p in range(2):
+        sizes = [(Info.strip_w[p], Info.strip_h[p])]
+        for _ in range(2):
+            sizes.append(tuple((v + 1) // 2 for v in sizes[-1]))
+        n = [w * h for w, h in sizes]
+        for l in range(3):
+            want += 2 * n[l] * (4 + 20)
+            for _ in range(2):
+                if outer == 0:
+                    want += n[l] * (8 + 2)
+                for o in range(outer):
+                    want += n[l] * (24 + 4 + 8 + 8 + 32)
+                    if o > 0:
+                        want += n[l] * (8 + 8)
+                    elif l < 2:
+                        want += n[l + 1] * (8 + 8)
+                    if inner == 0:
+                        want += n[l] * 8
+                    for k in range(inner // 2):
+                        want += n[l] * (32 + 8 + 1 + 8 + (8 if k > 0 else 0))
+                if outer > 0 and l == 0:
+                    want += n[l] * 24
+    assert bench.var_bytes_per_frame(Info, outer, inner) == want
