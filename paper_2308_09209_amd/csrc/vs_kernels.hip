@@ -839,7 +839,7 @@ __global__ __launch_bounds__(256) void k_pyr_fused(const Batch B, int after)
 //
 // Bound by the VALU (25 M wavefront instructions per 4 x 1080p frame, most at 4
 // cycles) and its chains' latency at 5 wavefronts per SIMD.  4 x 1080p ring 73 -> 61
-// us, 8 x 4K 503 -> 436 us, with quotients by one reciprocal (hom_div), a path for
+// us, 8 x 4K 503 -> 430 us, with quotients by one reciprocal (hom_div), a path for
 // wavefronts inside one camera and one row per thread (512 threads) instead of two;
 // a like path for wavefronts inside one overlap needs 121 VGPRs: 79 and 575 us.
 // A thread's 4 pixels of a row: their 4 codes read at once, then per group of

@@ -28,7 +28,8 @@ __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint
 // The image of block (tile, unit) b: lane i holds where image i ends, so one
 // ballot counts the images that end at or before b.  (A walk over the table in the
 // kernel arguments is a dependent scalar load per image and tile: 8 images of
-// 256 x 1080, 32 -> 32, 62.9 us with it and 58.8 us without.)
+// 256 x 1080, 32 -> 32, 63.9 us with it and 62.2 us without; a training step on 16
+// images of 64 x 270 355 and 320 us.)
 static_assert(MAXI <= 64, "an image per lane");
 
 __device__ __forceinline__ int img_end(const ImgTable& T)
@@ -255,10 +256,11 @@ __global__ __launch_bounds__(256) void k_conv3x3(const uint16_t* __restrict__ X,
 // places with every second pair of pixels, so that the 4 pixels a group reads
 // lie in distinct banks.  Taps across a row's end are cleared by masks (4 pixels
 // each) laid down with the unit.
-// Bound by the partial sums' bytes (37 KB per unit at 32 -> 32, written and
-// read once): 16 images of 64 x 270, 32 -> 32, 25 us, and 11 us to add them
-// (2-byte global loads per fragment and one thread per sum: 118 and 252 us).  A
-// block that walks units with the next one's loads in flight: 25 us, one block per
+// Bound by memory and its latency: 16 images of 64 x 270, 32 -> 32, 85 MB (40 of them
+// the partial sums, 37 KB per unit) in 25 us, 3.4 TB/s; a wavefront waits for loads and
+// barriers half of its time, the LDS is busy 5 %, the matrix cores 19 %.  11 us to
+// add the sums (2-byte global loads per fragment and one thread per sum: 118 and 252 us).
+// A block that walks units with the next one's loads in flight: 25 us, one block per
 // unit: 27 us.
 // ---------------------------------------------------------------------------
 constexpr int WG_PIX = 256;
